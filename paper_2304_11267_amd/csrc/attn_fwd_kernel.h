@@ -112,12 +112,17 @@ struct Geom {
     static constexpr int kThreads = kWaves * 64;
     static constexpr int DK = (D + 15) / 16;                  // 16-deep k steps of Q K^T
     static constexpr int DN = (D + 31) / 32;                  // 32-row d tiles of O^T
-    static constexpr bool kOnes = (D % 32) != 0 && !kQuarter;   // padding rows carry the row sum
+    // At most 16 rows of O^T left over from whole 32-row tiles: they go through
+    // one sparse MFMA per 32 keys instead of two dense ones (step32's O^T).
+    static constexpr bool kSparse = D % 32 == 8 || D % 32 == 16;
+    static constexpr int DD = kSparse ? DN - 1 : DN;          // dense d tiles
+    static constexpr bool kOnes = (D % 32 == 8 || D % 32 == 24) && !kQuarter;   // padding rows carry the row sum
     static constexpr int kTileBytes = kTK * D * 2;            // one K or V tile
     static constexpr int kChunks = kTileBytes / 1024;         // 1 KiB wave copies per tile
     static constexpr int kBufBytes = kTileBytes * (kOnes ? 3 : 2);   // K, V (, constant block)
     static constexpr int kHalfBytes = 2 * kBufBytes;          // two buffers per key split
-    static constexpr int kMergeFloats = QB * (DN * 16 * 64 + 3 * 64);   // one wave's O^T, m, max, l
+    static constexpr int kRegs = 16 * DN - (kSparse ? 8 : 0);   // O^T registers with rows of O in them
+    static constexpr int kMergeFloats = QB * (kRegs * 64 + 3 * 64);   // one wave's O^T, m, max, l
     static constexpr int kMergeBytes = (kKS - 1) * kQW * kMergeFloats * 4;
     static constexpr int kLdsBytes = kKS * kHalfBytes > kMergeBytes ? kKS * kHalfBytes : kMergeBytes;
     static constexpr bool kFits = D >= 32 && D % 8 == 0 && kLdsBytes <= kMaxLds && (!kBig || QB == 2);
@@ -137,6 +142,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     using G = Geom<D, GEO>;
     constexpr int DK = G::DK;
     constexpr int DN = G::DN;
+    constexpr int DD = G::DD;
     constexpr int QB = G::QB;
     constexpr int kQW = G::kQW;
     constexpr int kWaves = G::kWaves;
@@ -246,11 +252,22 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     // 4*(g/2) .. +3 and d = 32n + 16*(g%2) .. +15; its lane i points at key
     // 4*(g/2) + i/4, d = 32n + 16*(g%2) + 4*(i%4) .. +3.
     int v_off[DN];
+    int v_idx = 0;   // places of the sparse tile's values (see step32)
     {
         const int g = lane >> 4, i = lane & 15;
         const int krow = 4 * (g >> 1) + (i >> 2);
+        if constexpr (G::kSparse) {
+            // tile DD: the lane's 16 lanes cover keys 16*(g/2) .. +15 and d = 32*DD +
+            // 8*(g%2) .. +7; it points at key {0, 1, 8, 9}[i/4] (+ 2 when i%4 >= 2)
+            // and 4 of those d.  The second read is 4 keys on.
+            const int key = 16 * (g >> 1) + ((i >> 2) & 1) + 8 * (i >> 3) + 2 * ((i >> 1) & 1);
+            const int ds = 32 * DD + 8 * (g & 1) + 4 * (i & 1);
+            v_off[DD] = ds < D ? TB + (key * D + ds) * 2
+                               : G::kOnes ? 2 * TB + (key * D + ds - D) * 2 : TB + (key * D + ds - 32) * 2;
+            v_idx = (i & 8) ? 0xeeee : 0x4444;
+        }
 #pragma unroll
-        for (int n = 0; n < DN; ++n) {
+        for (int n = 0; n < DD; ++n) {
             const int ds = 32 * n + 16 * (g & 1) + 4 * (i & 3);
             // past D: the constant block, or (without one) V columns 32
             // lower, whose finite products land in O^T rows never stored
@@ -368,7 +385,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int n = 0; n < DN; ++n) {
+            for (int n = 0; n < DD; ++n) {
                 const char* vb = buf + v_off[n] + (32 * sub + 16 * u) * D * 2;
                 const u32x2 lo = lds_read_tr(vb);
                 const u32x2 hi = lds_read_tr(vb + 8 * D * 2);
@@ -376,6 +393,34 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
                 for (int j = 0; j < QB; ++j) acc[j][n] = mfma32x32x16<ET>(a, pk[j][u], acc[j][n]);
             }
+        // The last 8 or 16 rows of V^T would fill a quarter or half of a dense
+        // tile.  As a sparse tile each takes two rows, one with the first and one
+        // with the last two of every four keys, and both 16-key steps take one
+        // instruction.  Rows 0..7 and 8..15 of the tile are the two parts of d =
+        // 32*DD .. +7, rows 16..23 and 24..31 those of the next 8 (or the row of ones).
+        if constexpr (G::kSparse) {
+            const char* vb = buf + v_off[DD] + 32 * sub * D * 2;
+            const u32x2 lo = lds_read_tr(vb);
+            const u32x2 hi = lds_read_tr(vb + 4 * D * 2);
+            const u32x4 a = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+            for (int j = 0; j < QB; ++j)
+                acc[j][DD] = smfmac32x32x32<ET>(a, pk[j][0], pk[j][1], acc[j][DD], v_idx);
+        }
+    };
+
+    // Add the two parts of the sparse tile's rows: registers 0..7 then hold d =
+    // 32*DD .. +15 as in a dense tile.
+    auto fold_sparse = [&]() __attribute__((always_inline)) {
+        if constexpr (G::kSparse) {
+#pragma unroll
+            for (int j = 0; j < QB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    acc[j][DD][r] += acc[j][DD][4 + r];
+                    acc[j][DD][4 + r] = acc[j][DD][8 + r] + acc[j][DD][12 + r];
+                }
+        }
     };
 
     std::integral_constant<bool, false> full_c;
@@ -396,7 +441,8 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         constexpr int NP = 2 * QB;               // (sub-tile, block) pairs
         f32x16 st[2][QB];
         u32x4 pk[2][QB][2];
-        u32x4 vt[2][2][DN];
+        u32x4 vt[2][2][DD > 0 ? DD : 1];
+        u32x4 vs[2];
         auto qk = [&](int sub) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < QB; ++j)
@@ -413,12 +459,18 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int n = 0; n < DN; ++n) {
+                for (int n = 0; n < DD; ++n) {
                     const char* vb = buf + v_off[n] + (32 * sub + 16 * u) * D * 2;
                     const u32x2 lo = lds_read_tr(vb);
                     const u32x2 hi = lds_read_tr(vb + 8 * D * 2);
                     vt[sub][u][n] = u32x4{lo[0], lo[1], hi[0], hi[1]};
                 }
+            if constexpr (G::kSparse) {
+                const char* vb = buf + v_off[DD] + 32 * sub * D * 2;
+                const u32x2 lo = lds_read_tr(vb);
+                const u32x2 hi = lds_read_tr(vb + 4 * D * 2);
+                vs[sub] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+            }
         };
         auto softmax = [&](int pr) __attribute__((always_inline)) {
             const int sub = pr / QB, j = pr % QB;
@@ -442,7 +494,9 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int n = 0; n < DN; ++n) acc[j][n] = mfma32x32x16<ET>(vt[sub][u][n], pk[sub][j][u], acc[j][n]);
+                for (int n = 0; n < DD; ++n) acc[j][n] = mfma32x32x16<ET>(vt[sub][u][n], pk[sub][j][u], acc[j][n]);
+            if constexpr (G::kSparse)
+                acc[j][DD] = smfmac32x32x32<ET>(vs[sub], pk[sub][j][0], pk[sub][j][1], acc[j][DD], v_idx);
         };
         qk(0);
         qk(1);
@@ -539,6 +593,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     };
 
     run_tiles(fixed_c);
+    fold_sparse();
     // Overflow vote: with m fixed at the first sub-tile's maximum - kPBias, a
     // later logit larger than that maximum by more than ~8 (log2) overflows
     // the rounded p to inf,
@@ -570,6 +625,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         if (any) {
             reset();
             run_tiles(online_c);
+            fold_sparse();
             // The merge below writes into the tile buffers; a wave of key
             // half 1 may still be reading its ragged last tile there (run_tiles
             // ends without a barrier after that tile).  The fixed-maximum pass
@@ -580,7 +636,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 
     // ---- merge the key splits of every row (the block-merge rule): split s
     // > 0 leaves its O^T, m, max and l in LDS, split 0 folds them in
-    constexpr int kMF = DN * 16 * 64 + 3 * 64;   // floats per query block
+    constexpr int kMF = G::kRegs * 64 + 3 * 64;   // floats per query block
     auto mrg_of = [&](int s) { return (float*)smem + ((s - 1) * kQW + wq) * G::kMergeFloats; };
     if (kh != 0) {
         float* mrg = mrg_of(kh);
@@ -588,12 +644,10 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         for (int j = 0; j < QB; ++j) {
             float* mj = mrg + j * kMF;
 #pragma unroll
-            for (int n = 0; n < DN; ++n)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mj[(n * 16 + r) * 64 + lane] = acc[j][n][r];
-            mj[DN * 16 * 64 + lane] = m_run[j];
-            mj[DN * 16 * 64 + 64 + lane] = s_max[j];
-            mj[DN * 16 * 64 + 128 + lane] = l_part[j];
+            for (int i = 0; i < G::kRegs; ++i) mj[i * 64 + lane] = acc[j][i / 16][i % 16];
+            mj[G::kRegs * 64 + lane] = m_run[j];
+            mj[G::kRegs * 64 + 64 + lane] = s_max[j];
+            mj[G::kRegs * 64 + 128 + lane] = l_part[j];
         }
     }
     __syncthreads();
@@ -603,17 +657,15 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
         const float* mj = mrg_of(s) + j * kMF;
-        const float m_b = mj[DN * 16 * 64 + lane];
+        const float m_b = mj[G::kRegs * 64 + lane];
         const float m_new = fmaxf(m_run[j], m_b);
         const float a0 = fast_exp2(m_run[j] - m_new);   // exp2(-inf) = 0 for an empty split
         const float a1 = fast_exp2(m_b - m_new);
 #pragma unroll
-        for (int n = 0; n < DN; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[j][n][r] = acc[j][n][r] * a0 + mj[(n * 16 + r) * 64 + lane] * a1;
-        s_max[j] = fmaxf(s_max[j], mj[DN * 16 * 64 + 64 + lane]);
-        l_part[j] = l_part[j] * a0 + mj[DN * 16 * 64 + 128 + lane] * a1;
+        for (int i = 0; i < G::kRegs; ++i)
+            acc[j][i / 16][i % 16] = acc[j][i / 16][i % 16] * a0 + mj[i * 64 + lane] * a1;
+        s_max[j] = fmaxf(s_max[j], mj[G::kRegs * 64 + 64 + lane]);
+        l_part[j] = l_part[j] * a0 + mj[G::kRegs * 64 + 128 + lane] * a1;
         m_run[j] = m_new;
     }
 

@@ -38,6 +38,27 @@ __device__ __forceinline__ f32x16 mfma32x32x16(u32x4 a, u32x4 b, f32x16 c) {
     }
 }
 
+// D += A * B on one 32x32x32 sparse matrix-core tile (in the time of the dense
+// 32x32x16).  B is 32 x 32: lane l holds column l % 32, b0 then b1.  Of A's row
+// l % 32, lane l holds 8 of the 16 values that meet the b0 (l < 32) or the b1
+// (l >= 32) of both lane halves: two of each four consecutive ones, in the
+// order b[0..3] and b[4..7] of lanes below 32, then of lanes from 32 on;
+// `idx` has the pair's places in their four, 2 bits each.
+template <int ET>
+__device__ __forceinline__ f32x16 smfmac32x32x32(u32x4 a, u32x4 b0, u32x4 b1, f32x16 c, int idx) {
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    const u32x8 b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+    if constexpr (ET == kF16) {
+        typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
+        return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, a),
+                                                        __builtin_bit_cast(f16x16, b), c, idx, 0, 0);
+    } else {
+        typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+        return __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                         __builtin_bit_cast(bf16x16, b), c, idx, 0, 0);
+    }
+}
+
 // Round two floats to the 16-bit type (nearest even) and pack them, x in the low half.
 // (one v_cvt_pk_f16_f32 / v_cvt_pk_bf16_f32)
 template <int ET>
