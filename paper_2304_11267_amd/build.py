@@ -21,7 +21,7 @@ PROBES_LIB = os.path.join(HERE, "libsdattn_probes.so")
 PROBE_SOURCES = ["probes.hip"]
 ARCH = "gfx950"
 
-SOURCES = ["attn_fwd.hip", "attn_fwd_bf16.hip", "attn_fwd_short.hip", "attn_fwd_generic.hip", "softmax_rows.hip",
+SOURCES = ["attn_fwd.hip", "attn_fwd_bf16.hip", "attn_fwd_stats.hip", "attn_fwd_short.hip", "attn_fwd_generic.hip", "softmax_rows.hip",
            "twopass.hip", "linear.hip", "norm_act.hip", "winograd.hip",
            "sdattn_api.hip"]
 
@@ -39,7 +39,11 @@ CFLAGS = [
 
 # Per-file additions.  The short-sequence kernel is latency-bound: its first 14
 # argument dwords arrive preloaded in SGPRs instead of through scalar loads.
+# The tiled kernel's maxima are of finite scores (NaN inputs give unspecified
+# outputs): without NaNs to honour each takes one instruction instead of two.
+_NO_NANS = ["-fno-honor-nans"]
 EXTRA_FLAGS = {
+    "attn_fwd.hip": _NO_NANS, "attn_fwd_bf16.hip": _NO_NANS, "attn_fwd_stats.hip": _NO_NANS,
     "attn_fwd_short.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=14"],
 }
 

@@ -6,7 +6,7 @@ namespace sdattn {
 
 hipError_t launch_attn_fwd_tiled_bf16(const AttnArgs& a) {
     using Seq = std::make_integer_sequence<int, 32>;   // D = 8, 16, ..., 256
-    return dispatch_d<kBF16>(a, Seq{});
+    return dispatch_d<kBF16, kPlain>(a, Seq{});
 }
 
 }  // namespace sdattn

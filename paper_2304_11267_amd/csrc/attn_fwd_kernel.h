@@ -11,9 +11,8 @@
 // read from LDS feeds two MFMAs.  Registers are budgeted for two waves per
 // SIMD (256 each), or for one (up to 512) where the LDS already limits a CU
 // to one wave per SIMD.
-// Key/value tiles of 64 keys (128 with 256-row workgroups) move through LDS
-// double-buffered per half: while
-// one tile is consumed the next is copied straight from global memory
+// Key/value tiles of 64 keys move through two to five LDS buffers per half:
+// while one tile is consumed the next are copied straight from global memory
 // (global_load_lds, 16 bytes per lane, no registers involved), keeping the
 // row-major [key][d] layout.  Per 32-key sub-tile, wave and query block:
 //
@@ -22,9 +21,9 @@
 //                    The accumulator puts one query per lane (lane % 32) and
 //                    16 of the 32 keys in that lane, so the row maximum needs a
 //                    single exchange between lane halves.
-//   p = 2^(c s - m)  c = |scale| log2(e), one FMA and one exponential per
-//                    score.  m is fixed at the maximum of each wave's first
-//                    sub-tile less kPBias = 8 (p may then exceed 1); a row
+//   p = 2^(c (s-m))  c = |scale| log2(e), one multiply (or FMA) and one
+//                    exponential per score.  m is fixed at the maximum of each
+//                    wave's first sub-tile less kPBias / c, kPBias = 8 (p may then exceed 1); a row
 //                    whose later logits would overflow the rounded p sends the
 //                    workgroup through an exact fallback in which m moves, with
 //                    the rescale of O and l, whenever a weight would pass 2^15.
@@ -44,9 +43,10 @@
 //                    O^T.  Otherwise the packed p pairs are summed with v_dot2
 //                    against (1, 1).
 //
-// With the maximum fixed, a whole 64-key tile is written as a software
-// pipeline, so that each step's softmax has the independent MFMAs of its
-// neighbours beside it, and left to the compiler's scheduler.
+// With the maximum fixed the pass is a software pipeline, so that each step's
+// softmax has the independent MFMAs of its neighbours beside it: over the whole
+// key range, in a written order, where the LDS holds the buffers for it
+// (stream_tiles); else over one 64-key tile, left to the compiler's scheduler.
 //
 // This is the block-wise ("multi-stage") reduction of Sec. 3.2.1 -- a block's
 // maximum and exponential sum merged into the running pair, and the key
@@ -72,15 +72,16 @@ namespace {
 // workgroup and keys per LDS tile.
 constexpr int kGeoSmall = 0;           // 64 rows, 64-key tiles
 constexpr int kGeoNormal = 1;          // 128 rows, 64-key tiles
-constexpr int kGeoBig = 2;             // 256 rows, 128-key tiles (QB = 2 only)
+constexpr int kGeoBig = 2;             // 256 rows, 64-key tiles (QB = 2 only)
 constexpr int kGeoQuarter = 3;         // 64 rows, keys split four ways, 64-key tiles
-// The exponent's reference m sits kPBias below the logit maximum it was
-// taken from (weights of the largest logits near 2^8; see p = 2^(c s - m)
+// The exponent's reference c m sits kPBias below the logit maximum it was
+// taken from (weights of the largest logits near 2^8; see p = 2^(c (s - m))
 // above); the online path moves m once a sub-tile's maximum would give a
 // weight above 2^kRescaleLimit (fp16 holds values below 2^16).
 constexpr float kPBias = 8.0f;
 constexpr float kRescaleLimit = 15.0f;
 constexpr int kMaxLds = 160 * 1024;
+constexpr int kDirectTiles = 4;         // tiles per key split up to which m moves from the start
 constexpr int kQuarterMinKeys = 512;   // shortest key sequence given to kGeoQuarter
 
 // QB = 32-row query blocks per wave.  With QB = 2 every K and V^T operand
@@ -91,9 +92,8 @@ constexpr int kQuarterMinKeys = 512;   // shortest key sequence given to kGeoQua
 // kGeoSmall halves the query waves of a workgroup (64 query rows instead of
 // 128), for calls whose 128-row blocks would leave CUs idle (fewer than 256
 // workgroups: the 32x32 and 16x16 levels).  kGeoBig doubles them (256 rows,
-// eight waves) and the keys per tile (128), for grids that still cover the
-// CUs: each K/V tile then serves twice the queries and a barrier twice the
-// keys, in the LDS the two 128-row workgroups of a CU would otherwise hold.
+// eight waves), for grids that still cover the CUs: each K/V tile then serves
+// twice the queries.
 // kGeoQuarter keeps kGeoSmall's 64 rows but splits the keys four ways
 // instead of two (eight waves), for small grids whose LDS would otherwise
 // leave one wave per SIMD: two waves then share each SIMD and hide each
@@ -105,7 +105,7 @@ struct Geom {
     static constexpr bool kBig = GEO == kGeoBig;
     static constexpr bool kQuarter = GEO == kGeoQuarter;
     static constexpr int kKS = kQuarter ? 4 : 2;              // key splits
-    static constexpr int kTK = kBig ? 128 : 64;               // keys per LDS tile
+    static constexpr int kTK = 64;                            // keys per LDS tile
     static constexpr int kQW = kBig ? 4 : (GEO == kGeoSmall || kQuarter ? 2 : 4) / QB;   // query waves
     static constexpr int kBQ = 32 * QB * kQW;                 // query rows per workgroup
     static constexpr int kWaves = kKS * kQW;                  // times the key splits
@@ -119,26 +119,45 @@ struct Geom {
     static constexpr bool kOnes = (D % 32 == 8 || D % 32 == 24) && !kQuarter;   // padding rows carry the row sum
     static constexpr int kTileBytes = kTK * D * 2;            // one K or V tile
     static constexpr int kChunks = kTileBytes / 1024;         // 1 KiB wave copies per tile
-    static constexpr int kBufBytes = kTileBytes * (kOnes ? 3 : 2);   // K, V (, constant block)
-    static constexpr int kHalfBytes = 2 * kBufBytes;          // two buffers per key split
+    static constexpr int kBufBytes = 2 * kTileBytes;          // K, V
+    static constexpr int kConstBytes = kOnes ? kTileBytes : 0;   // the constant block
+    // The streaming loop (stream_tiles) works on two tiles at once and takes a
+    // ring of three buffers per key split (five where a workgroup fills a CU and
+    // meets only every second tile); the other loop takes two.  It needs two
+    // query blocks a wave (each LDS operand then feeds two MFMAs; with one the LDS
+    // is as busy as the matrix core).  16 heads, us: 4096 keys D = 40 62.1 -> 56.1,
+    // D = 64 86.5 -> 76.0, D = 32 55.1 -> 52.3, D = 48 64.5 -> 65.5; 2048 keys
+    // D = 64 28.3 -> 25.3, D = 48 21.6 -> 20.1; 300 keys D = 40 7.9 -> 6.8.  The four
+    // key splits of kGeoQuarter leave it too few tiles each (1024 keys D = 40 9.5
+    // -> 10.1).
+    static constexpr int kRoom = kMaxLds - 64 - kConstBytes;
+    static constexpr bool kStream = QB == 2 && !kQuarter && kKS * 3 * kBufBytes <= kRoom;
+    static constexpr int kSlots = !kStream ? 2 : kBig && kKS * 5 * kBufBytes <= kRoom ? 5 : 3;
+    static constexpr int kStep = kSlots == 5 ? 2 : 1;         // tiles between two barriers of the streaming loop
+    static constexpr int kHalfBytes = kSlots * kBufBytes;
+    static constexpr int kConst = kKS * kHalfBytes;
     static constexpr int kRegs = 16 * DN - (kSparse ? 8 : 0);   // O^T registers with rows of O in them
     static constexpr int kMergeFloats = QB * (kRegs * 64 + 3 * 64);   // one wave's O^T, m, max, l
     static constexpr int kMergeBytes = (kKS - 1) * kQW * kMergeFloats * 4;
-    static constexpr int kLdsBytes = kKS * kHalfBytes > kMergeBytes ? kKS * kHalfBytes : kMergeBytes;
-    static constexpr bool kFits = D >= 32 && D % 8 == 0 && kLdsBytes <= kMaxLds && (!kBig || QB == 2);
+    static constexpr int kTiles = kConst + kConstBytes;
+    static constexpr int kUsed = kTiles > kMergeBytes ? kTiles : kMergeBytes;
+    static constexpr int kVote = kStream ? kUsed : 0;         // overflow votes: their own words, or the idle first tile
+    static constexpr int kLdsBytes = kUsed + (kStream ? 64 : 0);
+    static constexpr bool kFits = D >= 32 && D % 8 == 0 && kLdsBytes <= kMaxLds &&
+                                  (!kBig || QB == 2);
     // Waves per SIMD the register budget is sized for: two (256 registers
     // each) when the LDS lets enough workgroups share a CU, else one, which
     // leaves a wave up to 512 registers (the matrix-core registers then take
     // what would otherwise spill to scratch) at no cost in occupancy.
     static constexpr int kWgPerCu = kLdsBytes <= kMaxLds ? kMaxLds / kLdsBytes : 1;
-    static constexpr int kWavesPerSimd = kWgPerCu * kWaves >= 8 ? 2 : 1;
+    static constexpr int kWavesPerSimd = kStream || kWgPerCu * kWaves >= 8 ? 2 : 1;
 };
 
 template <int ET, int D, bool STATS, bool OROWS, int GEO>
 __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerSimd)) void attn_fwd_lds_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ LS, int Lq, int Lk, float scale_abs, float c,
-    int neg, int nqb, int oh) {
+    float bias, int neg, int nqb, int oh) {
     using G = Geom<D, GEO>;
     constexpr int DK = G::DK;
     constexpr int DN = G::DN;
@@ -166,19 +185,8 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 
     const char* Kh = (const char*)(K + (size_t)bh * Lk * D);
     const char* Vh = (const char*)(V + (size_t)bh * Lk * D);
-    char* hbase = smem + kh * G::kHalfBytes;   // this split's two buffers
-
-    // Constant blocks (one per buffer): a one in column 0 of every row, zeros
-    // elsewhere.  Lanes whose d lies at or past D read these instead of V.
-    if constexpr (G::kOnes) {
-        const uint32_t one = from_float<ET>(1.0f);
-        for (int i = tid; i < 2 * G::kKS * (TB / 16); i += kThreads) {
-            const int b = i / (TB / 16), j = i - b * (TB / 16);
-            u32x4 w = {0u, 0u, 0u, 0u};
-            if ((j * 8) % D == 0) w[0] = one;
-            *(u32x4*)(smem + b * G::kBufBytes + 2 * TB + j * 16) = w;
-        }
-    }
+    const int hbase = kh * G::kHalfBytes;   // this split's buffers
+    const uint32_t lds0 = lds_offset(smem);
 
     // Tiles of this split: [t_first, t_first + t_count).  Split s takes
     // tiles s * nh .. s * nh + nh - 1 (nh = ceil(ntiles / kKS)), the last
@@ -190,45 +198,55 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     const int t_count = min(nh, max(0, ntiles - t_first));
 
     // Copy tile t of this split into its buffer b (the split's kQW waves issue
-    // the 1 KiB pieces wq, wq + kQW, ...).  Rows past Lk repeat row Lk - 1
-    // (finite data; their weights are forced to zero).
+    // the 1 KiB pieces wq, wq + kQW, ...).  What lies past the last key repeats
+    // its last 16 bytes (finite data; their weights are forced to zero).
     auto issue_tile = [&](int t, int b) __attribute__((always_inline)) {
-        const int kbase = t * kTK;
-        char* bufp = hbase + b * G::kBufBytes;
-        if (kbase + kTK <= Lk) {
-            // a full tile is one contiguous run of K (and of V) rows; byte
-            // offsets inside a head fit 32 bits (the launch checks Lk * D)
-            const uint32_t tile_off = (uint32_t)kbase * (2 * D) + lane * 16;
+        // a tile is one contiguous run of K (and of V) rows; byte offsets inside a
+        // head fit 32 bits (the launch checks Lk * D)
+        const uint32_t dst = lds0 + hbase + b * G::kBufBytes;
+        const uint32_t tile_off = (uint32_t)t * TB + lane * 16;
+        const uint32_t last = (uint32_t)Lk * (2 * D) - 16;   // a head's last 16 bytes
 #pragma unroll
-            for (int i = 0; i < (2 * G::kChunks + kQW - 1) / kQW; ++i) {
-                const int cidx = wq + kQW * i;
-                if (cidx < 2 * G::kChunks) {
-                    const bool isv = cidx >= G::kChunks;
-                    const int cc = isv ? cidx - G::kChunks : cidx;
-                    const char* src = isv ? Vh : Kh;
-                    __builtin_amdgcn_global_load_lds(src + (size_t)(tile_off + cc * 1024),
-                                                     (lds_void_t*)(bufp + (isv ? TB : 0) + cc * 1024),
-                                                     16, 0, 0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < (2 * G::kChunks + kQW - 1) / kQW; ++i) {
-                const int cidx = wq + kQW * i;
-                if (cidx < 2 * G::kChunks) {
-                    const bool isv = cidx >= G::kChunks;
-                    const int cc = isv ? cidx - G::kChunks : cidx;
-                    const int byte = cc * 1024 + lane * 16;
-                    const int row = byte / (2 * D);
-                    const int col = byte - row * (2 * D);
-                    const size_t goff = (size_t)min(kbase + row, Lk - 1) * (2 * D) + col;
-                    __builtin_amdgcn_global_load_lds((isv ? Vh : Kh) + goff,
-                                                     (lds_void_t*)(bufp + (isv ? TB : 0) + cc * 1024),
-                                                     16, 0, 0);
-                }
+        for (int i = 0; i < (2 * G::kChunks + kQW - 1) / kQW; ++i) {
+            const int cidx = wq + kQW * i;
+            if (cidx < 2 * G::kChunks) {
+                const bool isv = cidx >= G::kChunks;
+                const uint32_t off = tile_off + (isv ? cidx - G::kChunks : cidx) * 1024;
+                copy16_to_lds(isv ? Vh : Kh, min(off, last), dst + cidx * 1024);
             }
         }
     };
+    // Workgroup barrier with the copies of at most `ahead` (0 to 2) of this
+    // wave's tiles still in flight.
+    auto barrier = [&](int ahead) __attribute__((always_inline)) {
+        constexpr int kMost = (2 * G::kChunks + kQW - 1) / kQW, kRem = 2 * G::kChunks % kQW;
+        __builtin_amdgcn_sched_barrier(0);
+        if (ahead <= 0) wait_copies<0>();
+        else if (ahead == 1 && (kRem == 0 || wq < kRem)) wait_copies<kMost>();
+        else if (ahead == 1) wait_copies<kMost - 1>();
+        else if (kRem == 0 || wq < kRem) wait_copies<2 * kMost>();
+        else wait_copies<2 * (kMost - 1)>();
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    if constexpr (G::kStream) {
+#pragma unroll
+        for (int i = 0; i < G::kSlots - G::kStep; ++i)
+            if (i < t_count) issue_tile(t_first + i, i);
+    }
+
+    // Constant block: a one in column 0 of every row, zeros elsewhere.  Lanes
+    // whose d lies at or past D read it instead of V.
+    if constexpr (G::kOnes) {
+        const uint32_t one = from_float<ET>(1.0f);
+        for (int i = tid; i < TB / 16; i += kThreads) {
+            u32x4 w = {0u, 0u, 0u, 0u};
+            if ((i * 8) % D == 0) w[0] = one;
+            *(u32x4*)(smem + G::kConst + i * 16) = w;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
 
     // Q^T operand of block j: lane holds query q0 + 32j + l32, d = 16s + 8*half .. +7.
     u32x4 qreg[QB][DK];
@@ -252,33 +270,37 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     // 4*(g/2) .. +3 and d = 32n + 16*(g%2) .. +15; its lane i points at key
     // 4*(g/2) + i/4, d = 32n + 16*(g%2) + 4*(i%4) .. +3.
     int v_off[DN];
-    int v_idx = 0;   // places of the sparse tile's values (see step32)
+    int v_mask = -1;   // last d tile: 0 in the lanes that read the constant block
+    int v_idx = 0;     // places of the sparse tile's values (see step32)
     {
         const int g = lane >> 4, i = lane & 15;
         const int krow = 4 * (g >> 1) + (i >> 2);
-        if constexpr (G::kSparse) {
-            // tile DD: the lane's 16 lanes cover keys 16*(g/2) .. +15 and d = 32*DD +
-            // 8*(g%2) .. +7; it points at key {0, 1, 8, 9}[i/4] (+ 2 when i%4 >= 2)
-            // and 4 of those d.  The second read is 4 keys on.
-            const int key = 16 * (g >> 1) + ((i >> 2) & 1) + 8 * (i >> 3) + 2 * ((i >> 1) & 1);
-            const int ds = 32 * DD + 8 * (g & 1) + 4 * (i & 1);
-            v_off[DD] = ds < D ? TB + (key * D + ds) * 2
-                               : G::kOnes ? 2 * TB + (key * D + ds - D) * 2 : TB + (key * D + ds - 32) * 2;
-            v_idx = (i & 8) ? 0xeeee : 0x4444;
-        }
 #pragma unroll
-        for (int n = 0; n < DD; ++n) {
-            const int ds = 32 * n + 16 * (g & 1) + 4 * (i & 3);
+        for (int n = 0; n < DN; ++n) {
+            int key = krow, ds = 32 * n + 16 * (g & 1) + 4 * (i & 3);
+            if (G::kSparse && n == DD) {
+                // the sparse tile: the lane's 16 lanes cover keys 16*(g/2) .. +15 and
+                // d = 32n + 8*(g%2) .. +7; it points at key {0, 1, 8, 9}[i/4] (+ 2 when
+                // i%4 >= 2) and 4 of those d.  The second read is 4 keys on.
+                key = 16 * (g >> 1) + ((i >> 2) & 1) + 8 * (i >> 3) + 2 * ((i >> 1) & 1);
+                ds = 32 * n + 8 * (g & 1) + 4 * (i & 1);
+                v_idx = (i & 8) ? 0xeeee : 0x4444;
+            }
             // past D: the constant block, or (without one) V columns 32
             // lower, whose finite products land in O^T rows never stored
-            v_off[n] = ds < D ? TB + (krow * D + ds) * 2
-                              : G::kOnes ? 2 * TB + (krow * D + ds - D) * 2 : TB + (krow * D + ds - 32) * 2;
+            v_off[n] = ds < D ? TB + (key * D + ds) * 2
+                              : G::kOnes ? G::kConst + (key * D + ds - D) * 2 : TB + (key * D + ds - 32) * 2;
+            if (G::kOnes && ds >= D) v_mask = 0;
         }
     }
+    // address of d tile n's values in the V tile of the buffer at LDS offset buf
+    auto v_addr = [&](int buf, int n) __attribute__((always_inline)) -> const char* {
+        return smem + ((G::kOnes && n == DN - 1 ? buf & v_mask : buf) + v_off[n]);
+    };
 
     f32x16 acc[QB][DN];
-    float m_run[QB];   // running max used in the exponent (log2 units)
-    float s_max[QB];   // true running max of the raw scores
+    float m_run[QB];   // the exponent's reference m, in units of the raw scores
+    float s_max[QB];   // true running max of the raw scores (this lane's keys)
     float l_part[QB];  // this lane's part of the row sum (v_dot2 path)
     auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -294,21 +316,36 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     };
     reset();
 
-    // How a sub-tile treats the running maximum m (log2 units):
-    //   kFirst  the wave's first sub-tile: m = its row maximum - kPBias (O is
+    // p = 2^(c (s - m)).  How a sub-tile treats m (in raw score units; `bias` is
+    // kPBias / c):
+    //   kFirst  the wave's first sub-tile: m = its row maximum - bias (O is
     //           still 0)
-    //   kFixed  m stays; p = 2^(c s - m) may exceed 1, and if a later logit
-    //           exceeds the first sub-tile's maximum by more than ~8 the
-    //           rounded p overflows to inf, which the overflow vote after the
-    //           loop detects
+    //   kFixed  m stays; p may exceed 1, and if a later logit exceeds the first
+    //           sub-tile's maximum by more than ~8 (log2 units) the rounded p
+    //           overflows to inf, which the overflow vote after the loop detects
     //   kOnline m moves (with the rescale of O and l) to a sub-tile's maximum
-    //           - kPBias whenever that maximum exceeds m by more than
-    //           kRescaleLimit -- the fallback
+    //           - bias whenever that maximum would give a weight above
+    //           2^kRescaleLimit -- the fallback
     enum { kFirst = 0, kFixed = 1, kOnline = 2 };
+
+    // kOnline: move m (block j) for a row maximum mx, if any row of the wave has to.
+    // m = -inf before the first keys (also where c = 0, when nothing else moves it).
+    auto move_m = [&](int j, float mx) __attribute__((always_inline)) {
+        if (__any(m_run[j] == -__builtin_inff() || (mx - m_run[j]) * c > kRescaleLimit)) {
+            const float m_new = fmaxf(m_run[j], mx - bias);
+            const float alpha = m_run[j] == -__builtin_inff() ? 0.0f : fast_exp2((m_run[j] - m_new) * c);
+#pragma unroll
+            for (int n = 0; n < DN; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][n][r] *= alpha;
+            l_part[j] *= alpha;
+            m_run[j] = m_new;
+        }
+    };
 
     // One 32-key sub-tile (keys kbase ..) held at row offset `sub` * 32 of
     // the tile in buffer base `buf`.
-    auto step32 = [&](auto mode_c, auto tail_c, const char* buf, int sub, int kbase)
+    auto step32 = [&](auto mode_c, auto tail_c, int buf, int sub, int kbase)
                       __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_c)::value;
         constexpr bool TAIL = decltype(tail_c)::value;
@@ -320,7 +357,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             for (int r = 0; r < 16; ++r) st[j][r] = 0.0f;
 #pragma unroll
         for (int s = 0; s < DK; ++s) {
-            u32x4 a = *(const u32x4*)(buf + k_off + (32 * sub * D + 16 * s) * 2);
+            u32x4 a = *(const u32x4*)(smem + buf + k_off + (32 * sub * D + 16 * s) * 2);
 #pragma unroll
             for (int j = 0; j < QB; ++j) st[j] = mfma32x32x16<ET>(a, qreg[j][s], st[j]);
         }
@@ -339,27 +376,14 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
                 float mloc = st[j][0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, st[j][r]);
-                mloc = half_max(mloc);
                 s_max[j] = fmaxf(s_max[j], mloc);
-                if constexpr (MODE == kFirst) {
-                    m_run[j] = mloc * c - kPBias;
-                } else if constexpr (MODE == kOnline) {
-                    const float mb = mloc * c;
-                    if (__any(mb > m_run[j] + kRescaleLimit)) {
-                        const float m_new = fmaxf(m_run[j], mb - kPBias);
-                        const float alpha = fast_exp2(m_run[j] - m_new);
-#pragma unroll
-                        for (int n = 0; n < DN; ++n)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) acc[j][n][r] *= alpha;
-                        l_part[j] *= alpha;
-                        m_run[j] = m_new;
-                    }
-                }
+                if constexpr (MODE != kFixed) mloc = half_max(mloc);
+                if constexpr (MODE == kFirst) m_run[j] = mloc - bias;
+                else if constexpr (MODE == kOnline) move_m(j, mloc);
             }
-            // ---- p = 2^(c s - m), rounded to the input type
-            const float negm = -m_run[j];
+            // ---- p = 2^(c (s - m)), rounded to the input type
             float p[16];
+            const float negm = -m_run[j] * c;
 #pragma unroll
             for (int r = 0; r < 16; ++r) p[r] = fast_exp2(fmaf(st[j][r], c, negm));
             if constexpr (TAIL) {
@@ -386,7 +410,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int n = 0; n < DD; ++n) {
-                const char* vb = buf + v_off[n] + (32 * sub + 16 * u) * D * 2;
+                const char* vb = v_addr(buf, n) + (32 * sub + 16 * u) * D * 2;
                 const u32x2 lo = lds_read_tr(vb);
                 const u32x2 hi = lds_read_tr(vb + 8 * D * 2);
                 const u32x4 a = {lo[0], lo[1], hi[0], hi[1]};
@@ -399,7 +423,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         // instruction.  Rows 0..7 and 8..15 of the tile are the two parts of d =
         // 32*DD .. +7, rows 16..23 and 24..31 those of the next 8 (or the row of ones).
         if constexpr (G::kSparse) {
-            const char* vb = buf + v_off[DD] + 32 * sub * D * 2;
+            const char* vb = v_addr(buf, DD) + 32 * sub * D * 2;
             const u32x2 lo = lds_read_tr(vb);
             const u32x2 hi = lds_read_tr(vb + 4 * D * 2);
             const u32x4 a = {lo[0], lo[1], hi[0], hi[1]};
@@ -429,7 +453,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     std::integral_constant<int, kFixed> fixed_c;
     std::integral_constant<int, kOnline> online_c;
 
-    // A whole 64-key tile with the maximum fixed, written as a software
+    // A whole 64-key tile, written as a software
     // pipeline over the (sub-tile, block) pairs P0 = (0, 0), P1 = (0, 1), ...:
     //   S^T of sub-tile 0, then S^T of sub-tile 1 beside the softmax of P0,
     //   then the P V product of P(k-1) beside the softmax of Pk, and last
@@ -437,7 +461,12 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     // so that each softmax has independent MFMAs next to it.  The compiler
     // schedules the whole tile: fences between these steps, or exponentials
     // pinned between the MFMAs, measured 1-2 % slower.
-    auto tile_fixed = [&](const char* buf) __attribute__((always_inline)) {
+    //
+    // In kOnline the tile's maximum (both sub-tiles, all rows at once) is taken
+    // between the S^T products and the softmax, and m moves where it has to: one
+    // look per tile, and the rest of the pipeline unchanged.
+    auto tile_pipe = [&](auto mode_c, int buf) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode_c)::value;
         constexpr int NP = 2 * QB;               // (sub-tile, block) pairs
         f32x16 st[2][QB];
         u32x4 pk[2][QB][2];
@@ -450,7 +479,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
                 for (int r = 0; r < 16; ++r) st[sub][j][r] = 0.0f;
 #pragma unroll
             for (int s = 0; s < DK; ++s) {
-                u32x4 a = *(const u32x4*)(buf + k_off + (32 * sub * D + 16 * s) * 2);
+                u32x4 a = *(const u32x4*)(smem + buf + k_off + (32 * sub * D + 16 * s) * 2);
     #pragma unroll
                 for (int j = 0; j < QB; ++j) st[sub][j] = mfma32x32x16<ET>(a, qreg[j][s], st[sub][j]);
             }
@@ -460,13 +489,13 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int n = 0; n < DD; ++n) {
-                    const char* vb = buf + v_off[n] + (32 * sub + 16 * u) * D * 2;
+                    const char* vb = v_addr(buf, n) + (32 * sub + 16 * u) * D * 2;
                     const u32x2 lo = lds_read_tr(vb);
                     const u32x2 hi = lds_read_tr(vb + 8 * D * 2);
                     vt[sub][u][n] = u32x4{lo[0], lo[1], hi[0], hi[1]};
                 }
             if constexpr (G::kSparse) {
-                const char* vb = buf + v_off[DD] + 32 * sub * D * 2;
+                const char* vb = v_addr(buf, DD) + 32 * sub * D * 2;
                 const u32x2 lo = lds_read_tr(vb);
                 const u32x2 hi = lds_read_tr(vb + 4 * D * 2);
                 vs[sub] = u32x4{lo[0], lo[1], hi[0], hi[1]};
@@ -476,7 +505,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             const int sub = pr / QB, j = pr % QB;
             float p[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) p[r] = fast_exp2(fmaf(st[sub][j][r], c, -m_run[j]));
+            for (int r = 0; r < 16; ++r) p[r] = fast_exp2(fmaf(st[sub][j][r], c, -m_run[j] * c));
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -500,6 +529,20 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         };
         qk(0);
         qk(1);
+        if constexpr (MODE == kOnline || STATS) {
+#pragma unroll
+            for (int j = 0; j < QB; ++j) {
+                float mx = fmaxf(st[0][j][0], st[1][j][0]), my = fmaxf(st[0][j][1], st[1][j][1]);
+#pragma unroll
+                for (int r = 2; r < 16; r += 2) {
+                    mx = fmaxf(mx, fmaxf(st[0][j][r], st[1][j][r]));
+                    my = fmaxf(my, fmaxf(st[0][j][r + 1], st[1][j][r + 1]));
+                }
+                mx = fmaxf(mx, my);
+                s_max[j] = fmaxf(s_max[j], mx);
+                if constexpr (MODE == kOnline) move_m(j, half_max(mx));
+            }
+        }
         read_vt(0);
         softmax(0);
 #pragma unroll
@@ -513,93 +556,290 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     };
 
     // consume the tile t (in buffer b) of this half; its first sub-tile in
-    // mode mode0_c, the others in mode_c.  A pipelined 64-key step reads its
-    // rows relative to the pointer it gets, so a 128-key tile is two of them.
+    // mode mode0_c, the others in mode_c.
     auto consume = [&](auto mode0_c, auto mode_c, int t, int b) __attribute__((always_inline)) {
-        const char* buf = hbase + b * G::kBufBytes;
+        const int buf = hbase + b * G::kBufBytes;
         const int kbase = t * kTK;
-        constexpr bool kPipelined = decltype(mode0_c)::value == kFixed &&
-                                    decltype(mode_c)::value == kFixed && !STATS;
+        // (kFirst is the pipeline's kOnline with nothing before it; the streaming
+        // kernels' kFixed has its own loop)
+        constexpr bool kPipelined = decltype(mode_c)::value == kOnline ||
+                                    (!G::kStream && decltype(mode0_c)::value == kFixed);
         if (kbase + kTK <= Lk) {
             if constexpr (kPipelined) {
-#pragma unroll
-                for (int h = 0; h < kTK / 64; ++h) tile_fixed(buf + h * 64 * D * 2);
+                tile_pipe(mode_c, buf);
             } else {
                 step32(mode0_c, full_c, buf, 0, kbase);
-#pragma unroll
-                for (int sb = 1; sb < kTK / 32; ++sb) step32(mode_c, full_c, buf, sb, kbase + 32 * sb);
+                step32(mode_c, full_c, buf, 1, kbase + 32);
             }
         } else {
             if (kbase + 32 <= Lk) step32(mode0_c, full_c, buf, 0, kbase);
             else step32(mode0_c, tail_c, buf, 0, kbase);
-#pragma unroll
-            for (int sb = 1; sb < kTK / 32; ++sb) {
-                const int kb = kbase + 32 * sb;
-                if (kb + 32 <= Lk) step32(mode_c, full_c, buf, sb, kb);
-                else if (kb < Lk) step32(mode_c, tail_c, buf, sb, kb);
-            }
+            const int kb = kbase + 32;
+            if (kb + 32 <= Lk) step32(mode_c, full_c, buf, 1, kb);
+            else if (kb < Lk) step32(mode_c, tail_c, buf, 1, kb);
         }
-    };
-
-    // The 64-key half h of the whole tile t (buffer b) of a 128-key geometry
-    // on the pipelined path.
-    auto consume_half = [&](int b, int h) __attribute__((always_inline)) {
-        tile_fixed(hbase + b * G::kBufBytes + h * 64 * D * 2);
     };
 
     // all tiles of this half: the first tile opens with kFirst, every other
     // sub-tile runs in mode_c (kFixed, or kOnline for the fallback)
     auto run_tiles = [&](auto mode_c) __attribute__((always_inline)) {
         if (t_count > 0) issue_tile(t_first, 0);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        barrier(0);
         if (t_count > 0) {
             if (t_count > 1) issue_tile(t_first + 1, 1);
             consume(first_c, mode_c, t_first, 0);
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        barrier(0);
         // Inside the loop only whole tiles are consumed; a ragged last tile
         // (the last tile of its half: nothing is copied over it afterwards)
         // waits in its buffer until the loop ends.  With a single way through
         // the loop body the accumulators keep their registers across
         // iterations instead of being copied at a join.
-        // With 128-key tiles on the fixed-maximum path the workgroup also
-        // meets between the two 64-key halves of every tile (faster at the
-        // 64x64 level while the tile's steps were fenced, neutral since);
-        // that barrier sits outside the conditions so every wave of both key
-        // halves reaches it.
-        constexpr bool kMidBarrier = G::kBig && decltype(mode_c)::value == kFixed && !STATS;
         int pend = -1;
         for (int i = 1; i < nh; ++i) {
             const int b = i & 1;
             if (i + 1 < t_count) issue_tile(t_first + i + 1, b ^ 1);
-            if constexpr (kMidBarrier) {
-                const bool whole = i < t_count && (t_first + i + 1) * kTK <= Lk;
-                if (i < t_count && !whole) pend = i;
-                if (whole) consume_half(b, 0);
-                __syncthreads();
-                if (whole) consume_half(b, 1);
-            } else {
-                if (i < t_count) {
-                    if ((t_first + i + 1) * kTK <= Lk) consume(mode_c, mode_c, t_first + i, b);
-                    else pend = i;
-                }
+            if (i < t_count) {
+                if ((t_first + i + 1) * kTK <= Lk) consume(mode_c, mode_c, t_first + i, b);
+                else pend = i;
             }
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
+            barrier(0);
         }
         if (pend >= 0) consume(mode_c, mode_c, t_first + pend, pend & 1);
     };
 
-    run_tiles(fixed_c);
-    fold_sparse();
-    // Overflow vote: with m fixed at the first sub-tile's maximum - kPBias, a
+    // The fixed-maximum pass as one stream over the wave's (32-key sub-tile,
+    // query block) pairs p = 0, 1, ...: step p issues
+    //   S^T of pair p + 2,  p of pair p + 1,  O^T += of pair p
+    // which do not depend on each other, a few exponentials behind each MFMA, in
+    // the order written here (sched_barrier keeps it).  A wave issues in order,
+    // so a run of MFMAs or of exponentials leaves the other unit idle; measured
+    // on the bare mix of D = 40 (6 MFMAs, 16 multiplies, 16 exponentials, 8
+    // conversions, two waves a SIMD), 198 clocks of MFMA and 233 of VALU take
+    // 277 interleaved, 314 as two runs.  m enters as the initial value of S^T,
+    // so that one multiply is left before the exponential.  Pair p's S^T and
+    // rounded p live in the buffers of p's parity.  64x64 level (B2 H8 L4096 D40):
+    // 62.0 -> 56.9 us; what bounds it is the power limit (the clock sits at 1.5 to
+    // 1.6 GHz) on 6 MFMAs, 16 exponentials and 24 other operations per pair, then
+    // the barriers, copies and LDS reads (35, 27 and 30 of 385 clocks a pair with
+    // a barrier per tile; one per two tiles and scalar copy addresses: 363).
+    auto stream_tiles = [&]() __attribute__((always_inline)) {
+        constexpr int SL = G::kSlots;
+        constexpr int NQ = DK;                                 // MFMAs of S^T
+        constexpr int NP = 2 * DD + (G::kSparse ? 1 : 0);      // MFMAs of O^T
+        constexpr int NM = NQ + NP;
+        const int n_whole = max(0, min(t_count, Lk / kTK - t_first));
+
+        barrier(min(t_count, SL - G::kStep) - 1);   // tile 0 (the first SL - kStep were issued above)
+
+        u32x4 kf[2][DK];
+        u32x4 vf[2][2][DD > 0 ? DD : 1];
+        u32x4 vsf[2];
+        f32x16 st[2];
+        u32x4 pk[2][2];
+        f32x16 cin[QB];
+
+        auto read_k = [&](int buf, int sub, int s) __attribute__((always_inline)) {
+            kf[sub][s] = *(const u32x4*)(smem + buf + k_off + (32 * sub * D + 16 * s) * 2);
+        };
+        // operand h of the O^T MFMAs (u = h / DD, n = h % DD; last the sparse one)
+        auto read_v = [&](int buf, int sub, int h) __attribute__((always_inline)) {
+            if (G::kSparse && h == 2 * DD) {
+                const char* vb = v_addr(buf, DD) + 32 * sub * D * 2;
+                const u32x2 lo = lds_read_tr(vb);
+                const u32x2 hi = lds_read_tr(vb + 4 * D * 2);
+                vsf[sub] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+            } else {
+                const int u = h / DD, n = h % DD;
+                const char* vb = v_addr(buf, n) + (32 * sub + 16 * u) * D * 2;
+                const u32x2 lo = lds_read_tr(vb);
+                const u32x2 hi = lds_read_tr(vb + 8 * D * 2);
+                vf[sub][u][n] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+            }
+        };
+        // The softmax of st[x] as a list of 2-score units, each stage one unit
+        // behind the one before: c s', 2^, rounding (and the row sum).  With
+        // statistics S^T starts from zero, for the exact maximum, and s - m is
+        // taken here.
+        constexpr int kIn = STATS ? 5 : 2, kOut = G::kOnes ? 1 : 2;
+        constexpr int kOps = 8 * (kIn + 2 + kOut);
+        auto softmax_op = [&](int x, int i) __attribute__((always_inline)) {
+            const int blk = QB == 2 ? x : 0;
+            int at = 0;
+#pragma unroll
+            for (int t = 0; t < 10; ++t) {
+                if (t < 8) {
+                    if (STATS) {
+                        if (i == at) s_max[blk] = fmaxf(s_max[blk], fmaxf(st[x][2 * t], st[x][2 * t + 1]));
+                        if (i == at + 1) st[x][2 * t] -= m_run[blk];
+                        if (i == at + 2) st[x][2 * t + 1] -= m_run[blk];
+                    }
+                    if (i == at + kIn - 2) st[x][2 * t] *= c;
+                    if (i == at + kIn - 1) st[x][2 * t + 1] *= c;
+                    at += kIn;
+                }
+                if (t >= 1 && t < 9) {
+                    if (i == at) st[x][2 * t - 2] = fast_exp2(st[x][2 * t - 2]);
+                    if (i == at + 1) st[x][2 * t - 1] = fast_exp2(st[x][2 * t - 1]);
+                    at += 2;
+                }
+                if (t >= 2) {
+                    const int w = t - 2;
+                    if (i == at) pk[x][w / 4][w % 4] = pack2<ET>(st[x][2 * w], st[x][2 * w + 1]);
+                    if (!G::kOnes && i == at + 1) l_part[blk] = add_pair<ET>(pk[x][w / 4][w % 4], l_part[blk]);
+                    at += kOut;
+                }
+            }
+        };
+        auto max_of = [&](int x) __attribute__((always_inline)) {
+            float m = st[x][0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) m = fmaxf(m, st[x][r]);
+            return m;
+        };
+        auto s_mfma = [&](int x, int sub, int s) __attribute__((always_inline)) {
+            const int blk = QB == 2 ? x : 0;
+            st[x] = mfma32x32x16<ET>(kf[sub][s], qreg[blk][s], s == 0 ? cin[blk] : st[x]);
+        };
+        auto o_mfma = [&](int x, int sub, int h) __attribute__((always_inline)) {
+            const int blk = QB == 2 ? x : 0;
+            if (G::kSparse && h == 2 * DD)
+                acc[blk][DN - 1] = smfmac32x32x32<ET>(vsf[sub], pk[x][0], pk[x][1], acc[blk][DN - 1], v_idx);
+            else
+                acc[blk][h % DD] = mfma32x32x16<ET>(vf[sub][h / DD][h % DD], pk[x][h / DD], acc[blk][h % DD]);
+        };
+        // Step of parity X on sub-tile s (its place SUB in the tile).  Step 0 reads the
+        // K of sub-tile s + 2 (kbuf), step 1 the V of s + 1 (vbuf): a whole sub-tile
+        // ahead of the MFMAs they feed.
+        auto step = [&](auto x_c, auto sub_c, int kbuf, int vbuf) __attribute__((always_inline)) {
+            constexpr int X = decltype(x_c)::value, SUB = decltype(sub_c)::value;
+#pragma unroll
+            for (int g = 0; g < NM; ++g) {
+                // S^T and O^T in turn; each is a chain on one accumulator, which two
+                // instructions in a row would wait on
+                const int q = (g * NQ + NM - 1) / NM, h = g - q;   // S^T and O^T MFMAs before this one
+                if ((g + 1) * NQ > q * NM) s_mfma(X, SUB ^ 1, q);
+                else o_mfma(X, SUB, !G::kSparse || h < DD ? h : h == DD ? 2 * DD : h - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (X == 0 && g < NQ) read_k(kbuf, SUB, g);
+                if (X == 1) {
+#pragma unroll
+                    for (int i = g * NP / NM; i < (g + 1) * NP / NM; ++i) read_v(vbuf, SUB ^ 1, i);
+                }
+#pragma unroll
+                for (int i = g * kOps / NM; i < (g + 1) * kOps / NM; ++i) softmax_op(1 - X, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        std::integral_constant<int, 0> x0;
+        std::integral_constant<int, 1> x1;
+
+        if (n_whole > 0) {
+            // pairs 0 and 1: their scores from zero, m from the first sub-tile's
+            // maximum, then the rounded p of pair 0
+            const int buf = hbase;
+#pragma unroll
+            for (int j = 0; j < QB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) cin[j][r] = 0.0f;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                if (x == 0) {
+#pragma unroll
+                    for (int s = 0; s < DK; ++s) read_k(buf, 0, s);
+                }
+#pragma unroll
+                for (int s = 0; s < DK; ++s) s_mfma(x, 0, s);
+            }
+#pragma unroll
+            for (int j = 0; j < QB; ++j) {
+                m_run[j] = half_max(max_of(j)) - bias;
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int blk = QB == 2 ? x : 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (!STATS) {
+                        st[x][r] -= m_run[blk];
+                        cin[blk][r] = -m_run[blk];
+                    }
+            }
+            if (STATS) s_max[0] = max_of(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st[0][r] = fast_exp2(STATS ? (st[0][r] - m_run[0]) * c : st[0][r] * c);
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                pk[0][w / 4][w % 4] = pack2<ET>(st[0][2 * w], st[0][2 * w + 1]);
+                if (!G::kOnes) l_part[0] = add_pair<ET>(pk[0][w / 4][w % 4], l_part[0]);
+            }
+#pragma unroll
+            for (int s = 0; s < DK; ++s) read_k(buf, 1, s);
+#pragma unroll
+            for (int h = 0; h < NP; ++h) read_v(buf, 0, h);
+        }
+        int slot = 0;
+        float s_last = 0.0f, l_last = 0.0f;
+        for (int i = 0; i < nh; i += G::kStep) {
+            // Tiles up to i + kStep are in LDS for every wave, and the buffers of the
+            // tiles before i are free for the next kStep copies.
+            barrier(min(t_count - 1, i + SL - 1 - G::kStep) - (i + G::kStep));
+#pragma unroll
+            for (int k = 0; k < G::kStep; ++k) {
+                const int t = i + SL - G::kStep + k;
+                const int b = slot - G::kStep + k;
+                if (t < t_count) issue_tile(t_first + t, b < 0 ? b + SL : b);
+            }
+#pragma unroll
+            for (int k = 0; k < G::kStep; ++k) {
+                const int cur = hbase + slot * G::kBufBytes;
+                slot = slot + 1 == SL ? 0 : slot + 1;
+                const int nxt = hbase + slot * G::kBufBytes;
+                if (i + k < n_whole) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    step(x0, x0, nxt, 0);
+                    step(x1, x0, 0, cur);
+                    step(x0, x1, nxt, 0);
+                    // the last step of a tile takes the softmax of the next tile's first
+                    // pair: what it adds is dropped below if there is none
+                    s_last = s_max[0];
+                    l_last = l_part[0];
+                    step(x1, x1, 0, nxt);
+                }
+            }
+        }
+        if (n_whole > 0) {
+            s_max[0] = s_last;
+            l_part[0] = l_last;
+        }
+        // a ragged last tile is the one after the whole ones; its copy has been
+        // waited for by the barrier of the step before
+        if (n_whole < t_count) {
+            const int t = t_first + n_whole, b = n_whole % SL;
+            if (n_whole > 0) consume(fixed_c, fixed_c, t, b);
+            else consume(first_c, fixed_c, t, b);
+        }
+    };
+
+    // With few tiles and one query block a moving m costs little beside the fixed
+    // part, and rows with large logits need no second pass: 16x16 level 8.2 us
+    // either way, with queries four times as long 12.6 -> 8.4; 32x32 level 12.3 ->
+    // 12.4 and 21.4 -> 12.6 (two query blocks: D = 64 there 12.2 -> 13.8, so not for
+    // them).  At large D a ragged tile's steps are code of their own to fetch
+    // (Lk 300, D = 160: 10.7 -> 11.9), so whole tiles only.  bf16 weights do not
+    // overflow.
+    const bool direct = !G::kStream && QB == 1 && ET == kF16 && nh <= kDirectTiles &&
+                        (DN <= 3 || Lk % kTK == 0);
+    // Overflow vote: with m fixed at the first sub-tile's maximum - bias, a
     // later logit larger than that maximum by more than ~8 (log2) overflows
     // the rounded p to inf,
     // which makes this lane's row sum non-finite.  Any such row sends the
     // whole workgroup (it shares the LDS tiles) through the online path.
-    {
+    int redo = 1;   // (one copy of the online path's code)
+    if (!direct) {
+        if constexpr (G::kStream) stream_tiles();
+        else run_tiles(fixed_c);
+        fold_sparse();
         bool overflow = false;
 #pragma unroll
         for (int j = 0; j < QB; ++j) {
@@ -611,27 +851,32 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             } else {
                 l_check = l_part[j];
             }
-            overflow = overflow || !(__builtin_fabsf(l_check) < __builtin_inff());
+            overflow = overflow || (__float_as_uint(l_check) & 0x7f800000u) == 0x7f800000u;   // inf or NaN
         }
-        // workgroup-wide OR through the (now idle) first LDS words
-        int* vote = (int*)smem;
+        // workgroup-wide OR through LDS
+        int* vote = (int*)(smem + G::kVote);
         const int wave_overflow = __any(overflow) ? 1 : 0;   // ballot with every lane active
         if (lane == 0) vote[wave] = wave_overflow;
         __syncthreads();
-        int any = 0;
+        redo = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) any |= vote[w];
+        for (int w = 0; w < kWaves; ++w) redo |= vote[w];
         __syncthreads();
-        if (any) {
-            reset();
-            run_tiles(online_c);
-            fold_sparse();
-            // The merge below writes into the tile buffers; a wave of key
-            // half 1 may still be reading its ragged last tile there (run_tiles
-            // ends without a barrier after that tile).  The fixed-maximum pass
-            // has the vote's barriers in between.
-            __syncthreads();
-        }
+    }
+    if (redo) {
+        reset();
+        run_tiles(online_c);
+        fold_sparse();
+        // The merge below writes into the tile buffers; a wave of key
+        // half 1 may still be reading its ragged last tile there (run_tiles
+        // ends without a barrier after that tile).  The fixed-maximum pass
+        // has the vote's barriers in between.
+        __syncthreads();
+    }
+
+    if constexpr (STATS) {
+#pragma unroll
+        for (int j = 0; j < QB; ++j) s_max[j] = half_max(s_max[j]);
     }
 
     // ---- merge the key splits of every row (the block-merge rule): split s
@@ -652,15 +897,16 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     }
     __syncthreads();
     if (kh != 0) return;
-#pragma unroll
+#pragma unroll QB == 1 ? G::kKS : 1   // with two blocks one split's values in registers at a time
     for (int s = 1; s < G::kKS; ++s)
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
         const float* mj = mrg_of(s) + j * kMF;
         const float m_b = mj[G::kRegs * 64 + lane];
         const float m_new = fmaxf(m_run[j], m_b);
-        const float a0 = fast_exp2(m_run[j] - m_new);   // exp2(-inf) = 0 for an empty split
-        const float a1 = fast_exp2(m_b - m_new);
+        // an empty split (m = -inf) weighs nothing, also where c = 0
+        const float a0 = m_run[j] == m_new ? 1.0f : m_run[j] == -__builtin_inff() ? 0.0f : fast_exp2((m_run[j] - m_new) * c);
+        const float a1 = m_b == m_new ? 1.0f : m_b == -__builtin_inff() ? 0.0f : fast_exp2((m_b - m_new) * c);
 #pragma unroll
         for (int i = 0; i < G::kRegs; ++i)
             acc[j][i / 16][i % 16] = acc[j][i / 16][i % 16] * a0 + mj[i * 64 + lane] * a1;
@@ -703,7 +949,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
                 // Eq. 4 in natural units: L = max_j scale q.k, S = sum_j exp(scale q.k - L)
                 float* o2 = LS + ((size_t)bh * Lq + qrow) * 2;
                 o2[0] = s_max[j] * scale_abs;
-                o2[1] = l * fast_exp2(m_run[j] - s_max[j] * c);
+                o2[1] = l * fast_exp2((m_run[j] - s_max[j]) * c);
             }
         }
     }
@@ -716,6 +962,7 @@ hipError_t launch_kernel(const AttnArgs& a) {
     const long long nblk = (long long)a.B * a.H * nqb;
     const float scale_abs = a.scale < 0 ? -a.scale : a.scale;
     const float c = scale_abs * kLog2e;
+    const float bias = c > 1e-30f ? kPBias / c : 0.0f;   // scale 0: every weight is 1 whatever m
     auto kern = attn_fwd_lds_kernel<ET, D, STATS, OROWS, GEO>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -723,12 +970,41 @@ hipError_t launch_kernel(const AttnArgs& a) {
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(G::kThreads), G::kLdsBytes,
                        (hipStream_t)a.stream, (const uint16_t*)a.q, (const uint16_t*)a.k,
-                       (const uint16_t*)a.v, (uint16_t*)a.out, a.ls, a.Lq, a.Lk, scale_abs, c,
+                       (const uint16_t*)a.v, (uint16_t*)a.out, a.ls, a.Lq, a.Lk, scale_abs, c, bias,
                        a.scale < 0 ? 1 : 0, nqb, a.o_rows ? a.H : 0);
     return hipGetLastError();
 }
 
-template <int ET, int D>
+// The geometry with the largest workgroups whose grid still covers the 256 CUs
+// (the smallest one when none does).
+template <int ET, int D, bool STATS, bool OROWS>
+hipError_t launch_geo(const AttnArgs& a) {
+    const long long heads = (long long)a.B * a.H;
+    if (heads * ((a.Lq + 127) / 128) < 256) {
+        // keys split four ways (more waves per SIMD) once every split has at
+        // least two tiles; where the 128-row geometry streams only if one round of
+        // workgroups does it (B1 H8 L3960 D40, 496 workgroups: 41.0 us, against
+        // 31.8 in 248 of 128 rows)
+        const bool long_keys = a.Lk >= kQuarterMinKeys;
+        const bool one_round = heads * ((a.Lq + 63) / 64) <= 256;
+        if constexpr (Geom<D, kGeoQuarter>::kFits) {
+            if (long_keys && (one_round || !Geom<D, kGeoNormal>::kStream))
+                return launch_kernel<ET, D, STATS, OROWS, kGeoQuarter>(a);
+        }
+        if (!long_keys || one_round || !Geom<D, kGeoNormal>::kStream)
+            return launch_kernel<ET, D, STATS, OROWS, kGeoSmall>(a);
+    }
+    if constexpr (Geom<D, kGeoBig>::kFits) {
+        if (heads * ((a.Lq + 255) / 256) >= 256) return launch_kernel<ET, D, STATS, OROWS, kGeoBig>(a);
+    }
+    return launch_kernel<ET, D, STATS, OROWS, kGeoNormal>(a);
+}
+
+// Statistics and merged heads are instantiated apart (attn_fwd_stats.hip has
+// the former), so that the files compile side by side.
+enum { kPlain = 0, kStats = 1 };
+
+template <int ET, int D, int PART>
 hipError_t launch_d(const AttnArgs& a) {
     if constexpr (!Geom<D, kGeoNormal>::kFits || !Geom<D, kGeoSmall>::kFits) {
         return launch_attn_fwd_generic(a);
@@ -736,37 +1012,15 @@ hipError_t launch_d(const AttnArgs& a) {
         if (a.ls && a.o_rows) return hipErrorInvalidValue;   // no caller asks for both
         // tile copies address a head's K and V with 32-bit byte offsets
         if ((long long)a.Lk * D * 2 > 0x7fffffffLL) return launch_attn_fwd_generic(a);
-        if (a.ls) return launch_kernel<ET, D, true, false, kGeoNormal>(a);
-        // the geometry with the largest workgroups whose grid still covers the
-        // 256 CUs (the smallest one when none does)
-        const long long heads = (long long)a.B * a.H;
-        const bool small = heads * ((a.Lq + 127) / 128) < 256;
-        bool big = false;
-        if constexpr (Geom<D, kGeoBig>::kFits) big = heads * ((a.Lq + 255) / 256) >= 256;
-        if (small) {
-            // keys split four ways (two waves per SIMD) once every split has
-            // at least two tiles
-            if constexpr (Geom<D, kGeoQuarter>::kFits) {
-                if (a.Lk >= kQuarterMinKeys)
-                    return a.o_rows ? launch_kernel<ET, D, false, true, kGeoQuarter>(a)
-                                    : launch_kernel<ET, D, false, false, kGeoQuarter>(a);
-            }
-            return a.o_rows ? launch_kernel<ET, D, false, true, kGeoSmall>(a)
-                            : launch_kernel<ET, D, false, false, kGeoSmall>(a);
-        }
-        if constexpr (Geom<D, kGeoBig>::kFits) {
-            if (big) return a.o_rows ? launch_kernel<ET, D, false, true, kGeoBig>(a)
-                                     : launch_kernel<ET, D, false, false, kGeoBig>(a);
-        }
-        return a.o_rows ? launch_kernel<ET, D, false, true, kGeoNormal>(a)
-                        : launch_kernel<ET, D, false, false, kGeoNormal>(a);
+        if constexpr (PART == kStats) return launch_geo<ET, D, true, false>(a);
+        else return a.o_rows ? launch_geo<ET, D, false, true>(a) : launch_geo<ET, D, false, false>(a);
     }
 }
 
-template <int ET, int... Ds>
+template <int ET, int PART, int... Ds>
 hipError_t dispatch_d(const AttnArgs& a, std::integer_sequence<int, Ds...>) {
     hipError_t r = hipErrorInvalidValue;
-    bool hit = ((a.D == 8 * (Ds + 1) ? (r = launch_d<ET, 8 * (Ds + 1)>(a), true) : false) || ...);
+    bool hit = ((a.D == 8 * (Ds + 1) ? (r = launch_d<ET, 8 * (Ds + 1), PART>(a), true) : false) || ...);
     return hit ? r : hipErrorInvalidValue;
 }
 

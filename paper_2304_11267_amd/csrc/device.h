@@ -167,6 +167,27 @@ __device__ __forceinline__ u32x2 lds_read_tr(const char* p) {
     return __builtin_bit_cast(u32x2, v);
 }
 
+// Byte offset of an LDS pointer in the workgroup's LDS.
+__device__ __forceinline__ uint32_t lds_offset(const char* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// Copy 16 bytes per lane from base + off to LDS: lane l's go to dst + 16 l
+// (dst, a byte offset in the LDS, the same in every lane).  Unlike the builtin, the compiler does not see
+// this copy, so it puts no wait for it before LDS reads that cannot meet it;
+// the caller waits with wait_copies before reading what was copied.  M0 is left
+// changed: a kernel that uses this uses no builtin that goes through M0.
+__device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory");
+}
+// Wait until at most N of this wave's copies (and other vector loads) are in flight.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+    static_assert(N < 64, "vmcnt");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Where query row i of head bh = b*H + h goes in O: out_base(O, ...) + i * out_stride.
 // oh == 0: O is [B, H, Lq, D]; oh == H: O is [B, Lq, H*D] (the heads merged
 // into token rows).

@@ -1,0 +1,100 @@
+"""The tiled attention kernel's streaming loop and its geometries, and the path
+with a maximum that moves from the start, at the key counts where they change:
+one to five whole 64-key tiles a key split with and without a ragged one (a
+split without whole tiles, or without any), widths with and without the sparse
+tile and the row of ones, with statistics, large logits (the fallback, and rows
+whose maximum grows along the keys), zero and negative scale.  Against the fp64
+oracle with the parity suite's bound."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2304_11267_amd as sd
+from paper_2304_11267_amd import workloads as wl
+
+from parity_util import assert_close, to_device, to_host64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _needs_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    sd.load_library()
+
+
+def check(B, H, Lq, Lk, D, seed, dtype="f16", scale=None, q_mult=1.0, grow=False):
+    import torch
+    q, k, v = wl.make_qkv(B, H, Lq, Lk, D, seed, dtype, q_mult)
+    if grow:   # every key's logits outgrow the earlier ones'
+        k = (k.astype(np.float32) * np.linspace(0.2, 4.0, Lk, dtype=np.float32)[:, None]).astype(np.float16)
+    scale = float(np.float32(1 / np.sqrt(D))) if scale is None else scale
+    rows = None if Lq * Lk * B * H <= 1 << 23 else wl.sample_rows(B, H, Lq, 40, seed)
+    r, rl, rs, dev = oracle.attention(q, k, v, scale, dtype="bf16" if dtype == "bf16" else None, rows=rows,
+                                     want_dev=True)
+    qd, kd, vd = (to_device(t, dtype) for t in (q, k, v))
+    for stats in (False, True):
+        out = torch.full_like(qd, 7.0)
+        ls = torch.full((B, H, Lq, 2), 7.0, dtype=torch.float32, device="cuda") if stats else None
+        sd.forward_ex(qd, kd, vd, out, scale, ls=ls)
+        torch.cuda.synchronize()
+        g = to_host64(out)
+        g = g if rows is None else g.reshape(-1, D)[rows]
+        assert_close(g.reshape(r.shape), r, dtype=dtype, dev=dev,
+                     what=f"{B}x{H}x{Lq}x{Lk}x{D} {dtype} stats={stats}")
+        if stats:
+            got = ls.cpu().numpy().astype(np.float64).reshape(-1, 2)
+            got = got if rows is None else got[rows]
+            # L: an fp32 sum of D products (each at most |q| |k| by Cauchy-Schwarz);
+            # S: the weights' rounding, and L's error in the exponent
+            norm = [np.linalg.norm(to_host64(t), axis=-1).max() for t in (qd, kd)]
+            tol = D * 2.0 ** -23 * abs(scale) * norm[0] * norm[1]
+            assert np.all(np.abs(got[:, 0] - rl.reshape(-1)) <= tol)
+            eps = {"f16": 2.0 ** -10, "bf16": 2.0 ** -7}[dtype]
+            assert np.all(np.abs(got[:, 1] / rs.reshape(-1) - 1) <= eps + tol)
+
+
+# 2 key splits of 64-key tiles in the 128-row and 256-row geometries (4 and 5
+# buffers' wrap-around), D = 40 and 56 streaming
+@pytest.mark.parametrize("Lk", [129, 192, 255, 256, 257, 449, 640, 705, 1031])
+@pytest.mark.parametrize("D", [40, 56])
+def test_stream_128_rows(D, Lk):
+    check(2, 8, 2048, Lk, D, 900 + D + Lk)
+
+
+@pytest.mark.parametrize("Lk", [130, 321, 640, 1000])
+@pytest.mark.parametrize("D", [40, 64])
+def test_stream_256_rows(D, Lk):
+    check(2, 8, 4096, Lk, D, 1900 + D + Lk)
+
+
+@pytest.mark.parametrize("Lk", [130, 200, 448])
+def test_stream_64_rows(Lk):
+    check(1, 3, 70, Lk, 40, 2900 + Lk)
+
+
+# between one round of 64-row workgroups and the 128-row grid
+def test_stream_partial_grid():
+    check(1, 8, 2300, 600, 40, 3900)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("D", [40, 80, 160])
+def test_large_logits(D, dtype):
+    check(1, 4, 200, 333, D, 4900 + D, dtype, q_mult=4.0)
+    check(2, 8, 2048, 320, D, 4950 + D, dtype, q_mult=4.0)
+
+
+@pytest.mark.parametrize("D,Lk", [(40, 700), (80, 500), (80, 1000), (160, 500), (160, 1000)])
+def test_growing_keys(D, Lk):
+    check(1, 4, 150, Lk, D, 5900 + D + Lk, grow=True)
+    check(2, 8, 2048, Lk, D, 5950 + D + Lk, grow=True)
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.2, 1e-20, 1e-36])
+@pytest.mark.parametrize("D", [40, 80])
+def test_scales(D, scale):
+    check(1, 4, 150, 400, D, 6900 + D, scale=float(np.float32(scale)))
+    check(2, 8, 2048, 300, D, 6950 + D, scale=float(np.float32(scale)))
