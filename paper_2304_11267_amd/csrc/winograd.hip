@@ -49,7 +49,9 @@ __device__ constexpr float kAT[4][6] = {{1, 1, 1, 1, 1, 0},
 constexpr int kInTiles = 8;
 constexpr int kInChan = 64;
 constexpr int kPatchCols = 4 * kInTiles + 8;   // input columns staged: 4*tx0 - 4 .. 4*tx0 + 35
-constexpr int kPlane = 6 * kPatchCols + 8;     // halves per channel plane in LDS (padded)
+// halves per channel plane in LDS, padded so that the 32 channel pairs of a
+// read start in 16 different banks (61 * 4 words apart; at 6 * 40 + 8, 8 banks)
+constexpr int kPlane = 6 * kPatchCols + 4;
 // output transform: 16 tiles (64 pixels, whole output rows of 128 bytes) x 32
 // channels, one (tile, channel) per thread; the staged output rows are
 // [row][channel][68 halves], so that 32 consecutive channels land in 32
@@ -94,7 +96,7 @@ template <int ET>
 __global__ __launch_bounds__(256) void wino_input_kernel(const uint16_t* __restrict__ X,
                                                          uint16_t* __restrict__ V, int Ci, int H,
                                                          int W, int th, int tw, int nseg, int T) {
-    __shared__ uint16_t patch[kInChan * kPlane];
+    __shared__ __attribute__((aligned(16))) uint16_t patch[kInChan * kPlane];
     const int cb = blockIdx.y * kInChan;
     const int seg = blockIdx.x % nseg;
     const int brow = blockIdx.x / nseg;        // b * th + ty
@@ -148,15 +150,25 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const uint16_t* __restr
         const int cp = tid % (kInChan / 2), t = tid / (kInChan / 2);
         const int ch = 2 * cp;
         if (tx0 + t < tw && cb + ch < Ci) {
-            const uint16_t* src = patch + ch * kPlane + 4 * t + 3;   // global column 4*(tx0 + t) - 1
+            // row i of the patch: columns 4t + 3 .. 4t + 8 of the staged window (global
+            // column 4*(tx0 + t) - 1 on), as 4 + 8 + 4 aligned bytes
+            const uint16_t* src = patch + ch * kPlane + 4 * t;
             float d0[6][6], d1[6][6];
+            auto row = [&](const uint16_t* p, float* d) __attribute__((always_inline)) {
+                const uint32_t lo = *(const uint32_t*)(p + 2), hi = *(const uint32_t*)(p + 8);
+                const u32x2 mid = *(const u32x2*)(p + 4);
+                d[0] = to_float<ET>((uint16_t)(lo >> 16));
+                d[1] = to_float<ET>((uint16_t)mid[0]);
+                d[2] = to_float<ET>((uint16_t)(mid[0] >> 16));
+                d[3] = to_float<ET>((uint16_t)mid[1]);
+                d[4] = to_float<ET>((uint16_t)(mid[1] >> 16));
+                d[5] = to_float<ET>((uint16_t)hi);
+            };
 #pragma unroll
-            for (int i = 0; i < 6; ++i)
-#pragma unroll
-                for (int j = 0; j < 6; ++j) {
-                    d0[i][j] = to_float<ET>(src[i * kPatchCols + j]);
-                    d1[i][j] = to_float<ET>(src[kPlane + i * kPatchCols + j]);
-                }
+            for (int i = 0; i < 6; ++i) {
+                row(src + i * kPatchCols, d0[i]);
+                row(src + kPlane + i * kPatchCols, d1[i]);
+            }
             const size_t tg = (size_t)brow * tw + tx0 + t;   // tile index (b*th + ty)*tw + tx
             const size_t stride = (size_t)T * Ci;
             uint16_t* vo = V + tg * Ci + cb + ch;
