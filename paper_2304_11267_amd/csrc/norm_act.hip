@@ -5,16 +5,19 @@
 // Group normalisation.  Feature maps are channel-major, [B, C, HW], so group
 // (b, g) -- channels g*C/G .. (g+1)*C/G - 1 of batch b -- is one contiguous
 // run of n = (C/G)*HW values.  A workgroup of 512 threads reads a group's
-// run once into registers, 16 bytes per lane (n <= 49152 values: every UNet
-// level, 40960 at 64x64 with 320 channels), and keeps it: the mean, then the
-// mean square deviation from it (the two passes of the definition, over
-// registers), then y = x*a_c + b_c with a_c = gamma_c / sqrt(var + eps) and
-// b_c = beta_c - mean*a_c (gamma, beta staged in LDS).  With fewer than 256
-// groups, S = 2 or 4 workgroups share a group, all on one XCD: each computes
-// the statistics from the whole run (the later reads hit that XCD's L2) and
-// writes 1/S of the output, so the launch covers the chip.  Larger groups
-// (or pixel counts that are not a multiple of 8) take the same three steps
-// in one workgroup, reading the run from memory each time.
+// run once into registers, 16 bytes per lane (n <= 49152 values: every level of
+// a 64x64 latent), and keeps it: the mean, then the mean square deviation from
+// it (the two passes of the definition, over registers), then y = (x - mean)*a_c
+// + beta_c with a_c = gamma_c / sqrt(var + eps) (gamma, beta staged in LDS).
+// Longer runs take the same three steps with a read each.  With fewer than 256
+// groups, S = 2 or 4 workgroups share a group, all on one XCD: each computes the
+// statistics from the whole run (the later reads hit that XCD's L2) and writes
+// 1/S of the output, so the launch covers the chip.  Runs that do not start on
+// 16 bytes (HW not a multiple of 8) are read in the same aligned chunks, their
+// neighbours' values masked in the first and last.  Bound by the latency of one
+// read, two reductions and one write: [2, 320, 64, 64] 5.9 us; the odd sizes and
+// long runs, until then read value by value in one workgroup a group: figures at
+// launch_gn_e.
 //
 // GEGLU.  h [M, 2F] -> out[m, f] = h[m, f] * GELU(h[m, F + f]); 16 bytes of
 // each half per lane, one 16-byte store.  erf comes from the rational
@@ -64,8 +67,34 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
     return s;
 }
 
-template <int ET, int S>
-__global__ __launch_bounds__(kGnThreads) void gn_resident_kernel(
+// The run of n values starts `shift` values into the 16-byte chunk 0 (shift is 0
+// throughout when n is a multiple of 8).  Values of a chunk outside the run
+// come back as zeros; a chunk that ends past the tensor is read value by value.
+template <int ET, bool WHOLE>
+__device__ __forceinline__ u32x4 gn_load(const uint16_t* x0, int q, int shift, int n, long long left) {
+    if constexpr (WHOLE) {
+        return *(const u32x4*)(x0 + 8 * (size_t)q);
+    } else {
+        const int lo = max(0, shift - 8 * q), hi = min(8, shift + n - 8 * q);
+        if (lo == 0 && hi == 8) return *(const u32x4*)(x0 + 8 * (size_t)q);
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (8LL * q + 8 <= left) v = *(const u32x4*)(x0 + 8 * (size_t)q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t keep = 0xffffu << (16 * (e & 1));
+            if (e < lo || e >= hi) v[e >> 1] &= ~keep;
+            else if (8LL * q + 8 > left) v[e >> 1] |= (uint32_t)x0[8 * (size_t)q + e] << (16 * (e & 1));
+        }
+        return v;
+    }
+}
+
+// Group normalisation of runs of n < 2^30 values.  RESIDENT: the run stays in
+// registers; else each of the three steps reads it (from L2 after the first:
+// a group of the 96x96 level is 184 KB).  WHOLE: HW is a multiple of 8, so every
+// 16-byte chunk lies in one channel of one group.
+template <int ET, int S, bool RESIDENT, bool WHOLE>
+__global__ __launch_bounds__(kGnThreads) void gn_kernel(
     const uint16_t* X, const uint16_t* __restrict__ Gamma,
     const uint16_t* __restrict__ Beta, uint16_t* Y, int C, int HW, int G, int n, float eps,
     int ngroups) {
@@ -81,7 +110,11 @@ __global__ __launch_bounds__(kGnThreads) void gn_resident_kernel(
     const int g = bg % G;
     const int cpg = C / G;
     const size_t base = (size_t)bg * n;
-    const int nch = n / 8;
+    const int shift = WHOLE ? 0 : (int)(base & 7);
+    const uint16_t* x0 = X + (base - shift);
+    uint16_t* y0 = Y + (base - shift);
+    const long long left = (long long)((size_t)ngroups * n - (base - shift));   // values from x0 to the tensor's end
+    const int nch = (shift + n + 7) / 8;
     const int tid = threadIdx.x;
     const int lo = (int)((long long)nch * sp / S), hi = (int)((long long)nch * (sp + 1) / S);
     for (int i = tid; i < cpg; i += kGnThreads) {   // read beside x; used after the statistics
@@ -89,50 +122,82 @@ __global__ __launch_bounds__(kGnThreads) void gn_resident_kernel(
         bsh[i] = Beta ? to_float<ET>(Beta[g * cpg + i]) : 0.0f;
     }
 
-    u32x4 xr[kGnChunks];
+    u32x4 xr[RESIDENT ? kGnChunks : 1];
+    if constexpr (RESIDENT) {
 #pragma unroll
-    for (int j = 0; j < kGnChunks; ++j) {
-        const int q = tid + kGnThreads * j;
-        xr[j] = q < nch ? *(const u32x4*)(X + base + 8 * (size_t)q) : u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < kGnChunks; ++j) {
+            const int q = tid + kGnThreads * j;
+            xr[j] = q < nch ? gn_load<ET, WHOLE>(x0, q, shift, n, left) : u32x4{0u, 0u, 0u, 0u};
+        }
     }
+    // f(q, values) for this thread's chunks
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        if constexpr (RESIDENT) {
+#pragma unroll
+            for (int j = 0; j < kGnChunks; ++j)
+                if (tid + kGnThreads * j < nch) f(tid + kGnThreads * j, xr[j]);
+        } else {
+#pragma unroll 4
+            for (int q = tid; q < nch; q += kGnThreads) f(q, gn_load<ET, WHOLE>(x0, q, shift, n, left));
+        }
+    };
     float s = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kGnChunks; ++j) {
+    each([&](int, u32x4 v) __attribute__((always_inline)) {
         float f[8];
-        unpack8<ET>(xr[j], f);
+        unpack8<ET>(v, f);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s += f[e];   // chunks past the run hold zeros
-    }
+        for (int e = 0; e < 8; ++e) s += f[e];   // values outside the run are zero
+    });
     const float mean = block_sum(s, red) / (float)n;
     float s2 = 0.0f;
+    each([&](int q, u32x4 v) __attribute__((always_inline)) {
+        float f[8];
+        unpack8<ET>(v, f);
 #pragma unroll
-    for (int j = 0; j < kGnChunks; ++j) {
-        if (tid + kGnThreads * j < nch) {
-            float f[8];
-            unpack8<ET>(xr[j], f);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = f[e] - mean;
-                s2 = fmaf(d, d, s2);
-            }
+        for (int e = 0; e < 8; ++e) {
+            const int i = 8 * q + e - shift;
+            const float d = WHOLE || (i >= 0 && i < n) ? f[e] - mean : 0.0f;
+            s2 = fmaf(d, d, s2);
         }
-    }
+    });
     const float var = block_sum(s2, red) / (float)n;
     const float rstd = 1.0f / sqrtf(var + eps);
+    // (in place: S = 1, and every read of this run is behind block_sum's barriers
+    // before its first value is written, but for the re-read of a thread's own chunk)
+    each([&](int q, u32x4 v) __attribute__((always_inline)) {
+        if (q < lo || q >= hi) return;
+        float f[8];
+        unpack8<ET>(v, f);
+        if constexpr (WHOLE) {
+            const int cl = (8 * q) / HW;   // the chunk's channel in the group
+            const float a = rstd * gsh[cl], b = bsh[cl];
 #pragma unroll
-    for (int j = 0; j < kGnChunks; ++j) {
-        const int q = tid + kGnThreads * j;
-        if (q >= lo && q < hi) {
-            const int cl = (8 * q) / HW;   // the chunk's channel in the group (HW % 8 == 0)
-            const float a = rstd * gsh[cl];
-            const float b = fmaf(-mean, a, bsh[cl]);
-            float f[8];
-            unpack8<ET>(xr[j], f);
+            for (int e = 0; e < 8; ++e) f[e] = fmaf(f[e] - mean, a, b);
+            *(u32x4*)(y0 + 8 * (size_t)q) = pack8<ET>(f);
+        } else {
+            const int i0 = 8 * q - shift;
+            int cl = max(i0, 0) / HW;
+            int end = (cl + 1) * HW;       // first value of the next channel
+            float a = rstd * gsh[cl], b = bsh[cl];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) f[e] = fmaf(f[e], a, b);
-            *(u32x4*)(Y + base + 8 * (size_t)q) = pack8<ET>(f);
+            for (int e = 0; e < 8; ++e) {
+                if (i0 + e >= end && i0 + e < n) {
+                    ++cl;
+                    end += HW;
+                    a = rstd * gsh[cl];
+                    b = bsh[cl];
+                }
+                f[e] = fmaf(f[e] - mean, a, b);
+            }
+            if (i0 >= 0 && i0 + 8 <= n) {
+                *(u32x4*)(y0 + 8 * (size_t)q) = pack8<ET>(f);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (i0 + e >= 0 && i0 + e < n) y0[8 * (size_t)q + e] = from_float<ET>(f[e]);
+            }
         }
-    }
+    });
 }
 
 // Any group size: the three steps each read the run from memory.  (X and Y
@@ -215,12 +280,21 @@ template <int ET>
 hipError_t launch_gn_e(const GroupNormArgs& a) {
     const long long n = (long long)(a.C / a.G) * a.HW;
     const unsigned grid = (unsigned)(a.B * a.G);
-    if (a.HW % 8 == 0 && n <= kGnResident && a.C / a.G <= kGnMaxCpg) {
+    if (n < (1 << 30) && a.C / a.G <= kGnMaxCpg) {
         // several workgroups per group when there are few groups, unless in place
         const int ng = a.B * a.G;
         const int S = (ng >= 256 || a.x == a.y) ? 1 : ng >= 128 ? 2 : 4;
         const unsigned grid8 = (unsigned)((ng + 7) / 8 * 8 * S);
-        auto k = S == 1 ? gn_resident_kernel<ET, 1> : S == 2 ? gn_resident_kernel<ET, 2> : gn_resident_kernel<ET, 4>;
+        const bool whole = a.HW % 8 == 0;
+        const bool resident = n + (whole ? 0 : 14) <= kGnResident;
+        auto pick = [&](auto s_c) {
+            constexpr int K = decltype(s_c)::value;
+            return resident ? (whole ? gn_kernel<ET, K, true, true> : gn_kernel<ET, K, true, false>)
+                            : (whole ? gn_kernel<ET, K, false, true> : gn_kernel<ET, K, false, false>);
+        };
+        auto k = S == 1   ? pick(std::integral_constant<int, 1>{})
+                 : S == 2 ? pick(std::integral_constant<int, 2>{})
+                          : pick(std::integral_constant<int, 4>{});
         hipLaunchKernelGGL(k, dim3(grid8), dim3(kGnThreads), 0, (hipStream_t)a.stream,
                            (const uint16_t*)a.x, (const uint16_t*)a.gamma, (const uint16_t*)a.beta,
                            (uint16_t*)a.y, a.C, (int)a.HW, a.G, (int)n, a.eps, ng);
