@@ -1,4 +1,4 @@
-"""ctypes binding of libsdattn.so (argument marshalling only).
+"""Binding of libsdattn.so (argument marshalling only).
 
 Every function takes torch tensors that already live on the GPU, passes their
 device pointers, sizes and the current HIP stream to the C entry point of the
@@ -6,6 +6,11 @@ same name, and raises :class:`SdattnError` on a nonzero status.  No
 arithmetic of the attention happens here.  The library is loaded from the
 package directory on first use; a missing library raises, there is no other
 code path.
+
+The calls of a denoising loop are marshalled by the extension module _marshal
+(csrc/marshal.cpp): 10 us of Python and ctypes a call, as long as two of the
+smaller kernels, against 3.  What it does not take (it answers None) goes
+through ctypes below, which also raises the errors.
 """
 from __future__ import annotations
 
@@ -14,6 +19,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_NAME = "libsdattn.so"
+MARSHAL_NAME = "_marshal.so"
 
 STATUS_OK = 0
 STATUS_INVALID_ARG = 1
@@ -39,6 +45,8 @@ LAYOUT_ROWS = 0
 LAYOUT_HEADS = 1
 
 _lib = None
+_native = None   # the extension module; None: not loaded (or not built)
+_fn = {}         # address of each entry point it calls
 
 
 class SdattnError(RuntimeError):
@@ -106,8 +114,41 @@ def load_library():
     lib.sdattn_last_hip_error.restype = i32
     lib.sdattn_version.argtypes = []
     lib.sdattn_version.restype = ctypes.c_char_p
+    _load_marshal(lib)
     _lib = lib
     return lib
+
+
+def _load_marshal(lib):
+    """The extension module and the entry points' addresses in `lib`."""
+    global _native
+    path = os.path.join(HERE, MARSHAL_NAME)
+    if not os.path.exists(path):
+        return
+    import importlib.machinery
+    import importlib.util
+
+    import torch
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+    loader.exec_module(module)
+    get_device = getattr(torch._C, "_cuda_getDevice", None)
+    get_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if get_device is None or get_stream is None:
+        return
+    module.use_streams(get_device, get_stream)
+    for name in EXPORTS:
+        _fn[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    _native = module
+
+
+def _done(fn: str, status) -> bool:
+    """Whether the extension module has made the call (raises on a nonzero status)."""
+    if status is None:
+        return False
+    if status != STATUS_OK:
+        _check(fn, status)
+    return True
 
 
 def _check(fn: str, status: int):
@@ -155,6 +196,8 @@ def _expect(t, shape, like, name):
 
 def forward(q, k, v, out, scale: float, stream=None):
     """out = softmax(scale * q k^T) v for q/out [B,H,Lq,D], k/v [B,H,Lk,D], fp16."""
+    if _native and _done("sdattn_forward", _native.forward(_fn["sdattn_forward"], q, k, v, out, scale, stream)):
+        return out
     B, H, Lq, D = q.shape
     Lk = k.shape[2]
     _expect(k, (B, H, Lk, D), q, "k")
@@ -169,6 +212,8 @@ def forward(q, k, v, out, scale: float, stream=None):
 
 def forward_ex(q, k, v, out, scale: float, ls=None, stream=None):
     """forward for fp16 or bf16, optionally writing fp32 (L, S) per row to ls [B,H,Lq,2]."""
+    if _native and _done("sdattn_forward_ex", _native.forward_ex(_fn["sdattn_forward_ex"], q, k, v, out, ls, scale, stream)):
+        return out
     B, H, Lq, D = q.shape
     Lk = k.shape[2]
     _expect(k, (B, H, Lk, D), q, "k")
@@ -188,6 +233,8 @@ def forward_ex(q, k, v, out, scale: float, ls=None, stream=None):
 
 def softmax_rows(a, ls, p=None, scale: float = 1.0, stream=None):
     """Eq. 4 on a [rows, cols]: ls[r] = (L_r, S_r) fp32; p (optional) = exp(scale*a - L)/S."""
+    if _native and _done("sdattn_softmax_rows", _native.softmax_rows(_fn["sdattn_softmax_rows"], a, ls, p, scale, stream)):
+        return ls
     rows, cols = a.shape
     if ls.numel() != 2 * rows or ls.element_size() != 4:
         raise ValueError("ls must hold 2 float32 values per row")
@@ -203,6 +250,8 @@ def softmax_rows(a, ls, p=None, scale: float = 1.0, stream=None):
 
 def logits(q, k, a, scale: float, stream=None):
     """a = scale * q k^T: q [B,H,Lq,D], k [B,H,Lk,D] (fp16/bf16), a [B,H,Lq,Lk] (fp16/bf16/fp32)."""
+    if _native and _done("sdattn_logits", _native.logits(_fn["sdattn_logits"], q, k, a, scale, stream)):
+        return a
     B, H, Lq, D = q.shape
     Lk = k.shape[2]
     _expect(k, (B, H, Lk, D), q, "k")
@@ -216,6 +265,8 @@ def logits(q, k, a, scale: float, stream=None):
 
 def softmax_pv(a, ls, v, out, stream=None):
     """out = exp(a - L) / S times v, with (L, S) = ls [B,H,Lq,2] fp32 of a's rows."""
+    if _native and _done("sdattn_softmax_pv", _native.softmax_pv(_fn["sdattn_softmax_pv"], a, ls, v, out, stream)):
+        return out
     B, H, Lq, Lk = a.shape
     D = v.shape[3]
     _expect(v, (B, H, Lk, D), None, "v")
@@ -264,6 +315,9 @@ def attention_block_workspace(B, Lq, Lk, C):
 def attention_block(x, ctx, wq, wk, wv, wo, bo, out, workspace, heads, scale, stream=None):
     """SD's attention block: out = MHA(x, ctx) with weights [out, in]; workspace is a device
     tensor of at least attention_block_workspace(...) bytes."""
+    if _native and _done("sdattn_attention_block", _native.attention_block(
+            _fn["sdattn_attention_block"], x, ctx, wq, wk, wv, wo, bo, out, workspace, heads, scale, stream)):
+        return out
     B, Lq, C = x.shape
     Lk, Cc = ctx.shape[1], ctx.shape[2]
     _expect(ctx, (B, Lk, Cc), x, "ctx")
@@ -319,6 +373,9 @@ def project_kv(ctx, wk, wv, k, v, heads, stream=None):
 def attention_block_kv(x, wq, k, v, wo, bo, out, workspace, scale, stream=None):
     """The attention block with K and V given in heads layout [B, H, Lk, C/H];
     workspace of at least attention_block_workspace(B, Lq, 0, C) bytes."""
+    if _native and _done("sdattn_attention_block_kv", _native.attention_block_kv(
+            _fn["sdattn_attention_block_kv"], x, wq, k, v, wo, bo, out, workspace, scale, stream)):
+        return out
     B, Lq, C = x.shape
     H, Lk = k.shape[1], k.shape[2]
     _expect(k, (B, H, Lk, C // H), x, "k")
@@ -339,6 +396,9 @@ def attention_block_kv(x, wq, k, v, wo, bo, out, workspace, scale, stream=None):
 def group_norm(x, groups, y, gamma=None, beta=None, eps=1e-5, stream=None):
     """Group normalisation of channel-major feature maps x [B, C, ...] into y
     (same shape; y may be x); gamma, beta [C] or None."""
+    if _native and _done("sdattn_group_norm", _native.group_norm(
+            _fn["sdattn_group_norm"], x, groups, y, gamma, beta, eps, stream)):
+        return y
     B, C = x.shape[:2]
     HW = 1
     for d in x.shape[2:]:
@@ -357,6 +417,8 @@ def group_norm(x, groups, y, gamma=None, beta=None, eps=1e-5, stream=None):
 
 def geglu(h, out, stream=None):
     """out[..., f] = h[..., f] * GELU(h[..., F + f]) for h [..., 2F], out [..., F]."""
+    if _native and _done("sdattn_geglu", _native.geglu(_fn["sdattn_geglu"], h, out, stream)):
+        return out
     F2 = h.shape[-1]
     if F2 % 2:
         raise ValueError("h's last axis must have an even length")
@@ -388,6 +450,8 @@ def conv3x3_workspace(B, Ci, Co, H, W):
 def conv3x3(x, u, y, workspace, bias=None, stream=None):
     """y [B, Co, H, W] = 3x3 convolution (stride 1, zero padding 1) of x [B, Ci, H, W]
     with the transformed kernels u [36, Co, Ci] (from winograd_weights) + bias [Co]."""
+    if _native and _done("sdattn_conv3x3", _native.conv3x3(_fn["sdattn_conv3x3"], x, u, y, workspace, bias, stream)):
+        return y
     B, Ci, H, W = x.shape
     Co = u.shape[1]
     _expect(u, (36, Co, Ci), x, "u")

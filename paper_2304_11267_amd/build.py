@@ -4,6 +4,7 @@ Each csrc/*.hip file is compiled separately (in parallel) and linked into a
 shared library in the package directory, where the binding loads it.  The
 measurement kernels of include/sdattn_probes.h (csrc/probes.hip) go into a
 library of their own, libsdattn_probes.so, which only the benchmark loads.
+The binding's extension module (csrc/marshal.cpp) is built with g++.
 """
 from __future__ import annotations
 
@@ -19,6 +20,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsdattn.so")
 PROBES_LIB = os.path.join(HERE, "libsdattn_probes.so")
 PROBE_SOURCES = ["probes.hip"]
+MARSHAL = os.path.join(HERE, "_marshal.so")
 ARCH = "gfx950"
 
 SOURCES = ["attn_fwd.hip", "attn_fwd_bf16.hip", "attn_fwd_stats.hip", "attn_fwd_short.hip", "attn_fwd_generic.hip", "softmax_rows.hip",
@@ -73,11 +75,33 @@ def _link(objs, lib, verbose):
     os.replace(tmp, lib)
 
 
+def _build_marshal(verbose: bool) -> None:
+    """The binding's extension module (csrc/marshal.cpp), against this Python's torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = MARSHAL + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", sysconfig.get_paths()["include"]]
+    for inc in cpp_extension.include_paths():
+        cmd += ["-isystem", inc]
+    cmd += [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L", tdir, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = SOURCES + PROBE_SOURCES
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(srcs)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=len(srcs) + 1) as ex:
+        marshal = ex.submit(_build_marshal, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
+        marshal.result()
     _link(objs[:len(SOURCES)], LIB, verbose)
     _link(objs[len(SOURCES):], PROBES_LIB, verbose)
     return LIB
