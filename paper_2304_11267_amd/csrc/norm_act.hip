@@ -15,9 +15,9 @@
 // 1/S of the output, so the launch covers the chip.  Runs that do not start on
 // 16 bytes (HW not a multiple of 8) are read in the same aligned chunks, their
 // neighbours' values masked in the first and last.  Bound by the latency of one
-// read, two reductions and one write: [2, 320, 64, 64] 5.9 us; the odd sizes and
-// long runs, until then read value by value in one workgroup a group: figures at
-// launch_gn_e.
+// read, two reductions and one write: [2, 320, 64, 64] 5.7 us.  Against reading
+// value by value in one workgroup a group: [2, 320, 33, 62] 27.6 -> 6.1 us,
+// [2, 320, 90, 90] (runs past the registers) 99 -> 20.
 //
 // GEGLU.  h [M, 2F] -> out[m, f] = h[m, f] * GELU(h[m, F + f]); 16 bytes of
 // each half per lane, one 16-byte store.  erf comes from the rational
@@ -130,19 +130,20 @@ __global__ __launch_bounds__(kGnThreads) void gn_kernel(
             xr[j] = q < nch ? gn_load<ET, WHOLE>(x0, q, shift, n, left) : u32x4{0u, 0u, 0u, 0u};
         }
     }
-    // f(q, values) for this thread's chunks
-    auto each = [&](auto f) __attribute__((always_inline)) {
+    // f(q, values) for this thread's chunks (with PAST also for the zeros past the
+    // run that the registers hold: no condition to branch on)
+    auto each = [&](auto past_c, auto f) __attribute__((always_inline)) {
         if constexpr (RESIDENT) {
 #pragma unroll
             for (int j = 0; j < kGnChunks; ++j)
-                if (tid + kGnThreads * j < nch) f(tid + kGnThreads * j, xr[j]);
+                if (decltype(past_c)::value || tid + kGnThreads * j < nch) f(tid + kGnThreads * j, xr[j]);
         } else {
 #pragma unroll 4
             for (int q = tid; q < nch; q += kGnThreads) f(q, gn_load<ET, WHOLE>(x0, q, shift, n, left));
         }
     };
     float s = 0.0f;
-    each([&](int, u32x4 v) __attribute__((always_inline)) {
+    each(std::true_type{}, [&](int, u32x4 v) __attribute__((always_inline)) {
         float f[8];
         unpack8<ET>(v, f);
 #pragma unroll
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(kGnThreads) void gn_kernel(
     });
     const float mean = block_sum(s, red) / (float)n;
     float s2 = 0.0f;
-    each([&](int q, u32x4 v) __attribute__((always_inline)) {
+    each(std::false_type{}, [&](int q, u32x4 v) __attribute__((always_inline)) {
         float f[8];
         unpack8<ET>(v, f);
 #pragma unroll
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kGnThreads) void gn_kernel(
     const float rstd = 1.0f / sqrtf(var + eps);
     // (in place: S = 1, and every read of this run is behind block_sum's barriers
     // before its first value is written, but for the re-read of a thread's own chunk)
-    each([&](int q, u32x4 v) __attribute__((always_inline)) {
+    each(std::false_type{}, [&](int q, u32x4 v) __attribute__((always_inline)) {
         if (q < lo || q >= hi) return;
         float f[8];
         unpack8<ET>(v, f);
