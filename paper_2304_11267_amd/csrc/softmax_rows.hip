@@ -89,6 +89,16 @@ __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s
     m = M;
 }
 
+// The group of rows of workgroup i: each XCD takes a contiguous run of them,
+// last rows first.  The logits kernel writes A and softmax_pv reads it with
+// every XCD going forwards through its run, so this pass meets what was written
+// last while it is still in the 256 MB cache behind the L2s, and leaves there
+// what softmax_pv reads first (the three calls with A of 537 MB: 355.4 -> 350.8 us).
+__device__ __forceinline__ long long row_group(long long i, long long ngroups) {
+    return ngroups == gridDim.x ? ngroups - 1 - xcd_remap((int)i, (int)ngroups) : i;
+}
+
+
 // WPR = waves per row (1 or 4); VEC = rows are read in 16-byte chunks.
 template <int ET, int WPR, bool VEC>
 __global__ __launch_bounds__(kThreads) void softmax_rows_kernel(
@@ -104,7 +114,8 @@ __global__ __launch_bounds__(kThreads) void softmax_rows_kernel(
     const long long nunits = cols / EPC;          // chunks (or elements) per row
     const long long stride = 64LL * WPR;
 
-    for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
+    for (long long i = blockIdx.x; i < ngroups; i += gridDim.x) {
+        const long long g = row_group(i, ngroups);
         const long long row = g * RPW + wave / WPR;
         const bool live = row < rows;
         float m = -__builtin_inff(), s = 0.0f;
@@ -183,7 +194,8 @@ __global__ __launch_bounds__(kThreads) void softmax_rows_reg_kernel(
     const int wave = threadIdx.x >> 6;
     const int nunits = (int)(cols / EPC);
 
-    for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
+    for (long long it = blockIdx.x; it < ngroups; it += gridDim.x) {
+        const long long g = row_group(it, ngroups);
         const long long row = g * 4 + wave;
         if (row >= rows) continue;   // no barriers below: waves are independent
         const long long base = row * nunits;
