@@ -880,7 +880,10 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     }
 
     // ---- merge the key splits of every row (the block-merge rule): split s
-    // > 0 leaves its O^T, m, max and l in LDS, split 0 folds them in
+    // > 0 leaves its O^T, m, max and l in LDS, split 0 folds them in.  Its latency
+    // is all of a workgroup's last half microsecond, so: no branch for an empty
+    // split, all splits unrolled, 16 bytes a lane (four splits, 16 heads, 512 keys:
+    // D = 40 7.0 -> 6.2 us, D = 64 9.3 -> 8.5)
     constexpr int kMF = G::kRegs * 64 + 3 * 64;   // floats per query block
     auto mrg_of = [&](int s) { return (float*)smem + ((s - 1) * kQW + wq) * G::kMergeFloats; };
     if (kh != 0) {
@@ -889,7 +892,9 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         for (int j = 0; j < QB; ++j) {
             float* mj = mrg + j * kMF;
 #pragma unroll
-            for (int i = 0; i < G::kRegs; ++i) mj[i * 64 + lane] = acc[j][i / 16][i % 16];
+            for (int i = 0; i < G::kRegs; i += 4)
+                *(f32x4*)(mj + i * 64 + lane * 4) = f32x4{acc[j][i / 16][i % 16], acc[j][i / 16][i % 16 + 1],
+                                                          acc[j][i / 16][i % 16 + 2], acc[j][i / 16][i % 16 + 3]};
             mj[G::kRegs * 64 + lane] = m_run[j];
             mj[G::kRegs * 64 + 64 + lane] = s_max[j];
             mj[G::kRegs * 64 + 128 + lane] = l_part[j];
@@ -897,19 +902,24 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     }
     __syncthreads();
     if (kh != 0) return;
-#pragma unroll QB == 1 ? G::kKS : 1   // with two blocks one split's values in registers at a time
+#pragma unroll
     for (int s = 1; s < G::kKS; ++s)
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
         const float* mj = mrg_of(s) + j * kMF;
         const float m_b = mj[G::kRegs * 64 + lane];
         const float m_new = fmaxf(m_run[j], m_b);
-        // an empty split (m = -inf) weighs nothing, also where c = 0
-        const float a0 = m_run[j] == m_new ? 1.0f : m_run[j] == -__builtin_inff() ? 0.0f : fast_exp2((m_run[j] - m_new) * c);
-        const float a1 = m_b == m_new ? 1.0f : m_b == -__builtin_inff() ? 0.0f : fast_exp2((m_b - m_new) * c);
+        // an empty split (m = -inf, O and l zero) may have any finite weight: finite
+        // differences keep it so where c = 0
+        const float a0 = fast_exp2(fmaxf(m_run[j] - m_new, -__FLT_MAX__) * c);
+        const float a1 = fast_exp2(fmaxf(m_b - m_new, -__FLT_MAX__) * c);
 #pragma unroll
-        for (int i = 0; i < G::kRegs; ++i)
-            acc[j][i / 16][i % 16] = acc[j][i / 16][i % 16] * a0 + mj[i * 64 + lane] * a1;
+        for (int i = 0; i < G::kRegs; i += 4) {
+            const f32x4 w = *(const f32x4*)(mj + i * 64 + lane * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc[j][i / 16][i % 16 + e] = acc[j][i / 16][i % 16 + e] * a0 + w[e] * a1;
+        }
         s_max[j] = fmaxf(s_max[j], mj[G::kRegs * 64 + 64 + lane]);
         l_part[j] = l_part[j] * a0 + mj[G::kRegs * 64 + 128 + lane] * a1;
         m_run[j] = m_new;

@@ -98,3 +98,12 @@ def test_growing_keys(D, Lk):
 def test_scales(D, scale):
     check(1, 4, 150, 400, D, 6900 + D, scale=float(np.float32(scale)))
     check(2, 8, 2048, 300, D, 6950 + D, scale=float(np.float32(scale)))
+
+
+# four key splits of 64 rows, the last one without keys (9 tiles: 3 + 3 + 3 + 0) or
+# with a ragged tile only; scale 0 gives an empty split no weight of its own
+@pytest.mark.parametrize("scale", [None, 0.0, 1e-36])
+@pytest.mark.parametrize("Lk", [576, 577, 650])
+@pytest.mark.parametrize("D", [32, 40, 64, 80])
+def test_four_splits_with_an_empty_one(D, Lk, scale):
+    check(1, 4, 150, Lk, D, 7900 + D + Lk, scale=None if scale is None else float(np.float32(scale)))
