@@ -61,6 +61,7 @@
 
 #include <utility>
 
+#include "attn_geom.h"
 #include "device.h"
 #include "launch.h"
 
@@ -68,90 +69,13 @@ namespace sdattn {
 
 namespace {
 
-// Workgroup geometries (the GEO template argument): rows of queries per
-// workgroup and keys per LDS tile.
-constexpr int kGeoSmall = 0;           // 64 rows, 64-key tiles
-constexpr int kGeoNormal = 1;          // 128 rows, 64-key tiles
-constexpr int kGeoBig = 2;             // 256 rows, 64-key tiles (QB = 2 only)
-constexpr int kGeoQuarter = 3;         // 64 rows, keys split four ways, 64-key tiles
 // The exponent's reference c m sits kPBias below the logit maximum it was
 // taken from (weights of the largest logits near 2^8; see p = 2^(c (s - m))
 // above); the online path moves m once a sub-tile's maximum would give a
 // weight above 2^kRescaleLimit (fp16 holds values below 2^16).
 constexpr float kPBias = 8.0f;
 constexpr float kRescaleLimit = 15.0f;
-constexpr int kMaxLds = 160 * 1024;
 constexpr int kDirectTiles = 4;         // tiles per key split up to which m moves from the start
-constexpr int kQuarterMinKeys = 512;   // shortest key sequence given to kGeoQuarter
-
-// QB = 32-row query blocks per wave.  With QB = 2 every K and V^T operand
-// read from LDS feeds two MFMAs (half the LDS traffic per flop) and each wave
-// carries two independent MFMA / softmax chains; the register budget is then
-// sized for two waves per SIMD.
-//
-// kGeoSmall halves the query waves of a workgroup (64 query rows instead of
-// 128), for calls whose 128-row blocks would leave CUs idle (fewer than 256
-// workgroups: the 32x32 and 16x16 levels).  kGeoBig doubles them (256 rows,
-// eight waves), for grids that still cover the CUs: each K/V tile then serves
-// twice the queries.
-// kGeoQuarter keeps kGeoSmall's 64 rows but splits the keys four ways
-// instead of two (eight waves), for small grids whose LDS would otherwise
-// leave one wave per SIMD: two waves then share each SIMD and hide each
-// other's MFMA and exponential latencies.  Its tiles carry no constant
-// block (the LDS holds four splits' double buffers), so l comes from v_dot2.
-template <int D, int GEO = kGeoNormal>
-struct Geom {
-    static constexpr int QB = D <= 64 ? 2 : 1;
-    static constexpr bool kBig = GEO == kGeoBig;
-    static constexpr bool kQuarter = GEO == kGeoQuarter;
-    static constexpr int kKS = kQuarter ? 4 : 2;              // key splits
-    static constexpr int kTK = 64;                            // keys per LDS tile
-    static constexpr int kQW = kBig ? 4 : (GEO == kGeoSmall || kQuarter ? 2 : 4) / QB;   // query waves
-    static constexpr int kBQ = 32 * QB * kQW;                 // query rows per workgroup
-    static constexpr int kWaves = kKS * kQW;                  // times the key splits
-    static constexpr int kThreads = kWaves * 64;
-    static constexpr int DK = (D + 15) / 16;                  // 16-deep k steps of Q K^T
-    static constexpr int DN = (D + 31) / 32;                  // 32-row d tiles of O^T
-    // At most 16 rows of O^T left over from whole 32-row tiles: they go through
-    // one sparse MFMA per 32 keys instead of two dense ones (step32's O^T).
-    static constexpr bool kSparse = D % 32 == 8 || D % 32 == 16;
-    static constexpr int DD = kSparse ? DN - 1 : DN;          // dense d tiles
-    static constexpr bool kOnes = (D % 32 == 8 || D % 32 == 24) && !kQuarter;   // padding rows carry the row sum
-    static constexpr int kTileBytes = kTK * D * 2;            // one K or V tile
-    static constexpr int kChunks = kTileBytes / 1024;         // 1 KiB wave copies per tile
-    static constexpr int kBufBytes = 2 * kTileBytes;          // K, V
-    static constexpr int kConstBytes = kOnes ? kTileBytes : 0;   // the constant block
-    // The streaming loop (stream_tiles) works on two tiles at once and takes a
-    // ring of three buffers per key split (five where a workgroup fills a CU and
-    // meets only every second tile); the other loop takes two.  It needs two
-    // query blocks a wave (each LDS operand then feeds two MFMAs; with one the LDS
-    // is as busy as the matrix core).  16 heads, us: 4096 keys D = 40 62.1 -> 56.1,
-    // D = 64 86.5 -> 76.0, D = 32 55.1 -> 52.3, D = 48 64.5 -> 65.5; 2048 keys
-    // D = 64 28.3 -> 25.3, D = 48 21.6 -> 20.1; 300 keys D = 40 7.9 -> 6.8.  The four
-    // key splits of kGeoQuarter leave it too few tiles each (1024 keys D = 40 9.5
-    // -> 10.1).
-    static constexpr int kRoom = kMaxLds - 64 - kConstBytes;
-    static constexpr bool kStream = QB == 2 && !kQuarter && kKS * 3 * kBufBytes <= kRoom;
-    static constexpr int kSlots = !kStream ? 2 : kBig && kKS * 5 * kBufBytes <= kRoom ? 5 : 3;
-    static constexpr int kStep = kSlots == 5 ? 2 : 1;         // tiles between two barriers of the streaming loop
-    static constexpr int kHalfBytes = kSlots * kBufBytes;
-    static constexpr int kConst = kKS * kHalfBytes;
-    static constexpr int kRegs = 16 * DN - (kSparse ? 8 : 0);   // O^T registers with rows of O in them
-    static constexpr int kMergeFloats = QB * (kRegs * 64 + 3 * 64);   // one wave's O^T, m, max, l
-    static constexpr int kMergeBytes = (kKS - 1) * kQW * kMergeFloats * 4;
-    static constexpr int kTiles = kConst + kConstBytes;
-    static constexpr int kUsed = kTiles > kMergeBytes ? kTiles : kMergeBytes;
-    static constexpr int kVote = kStream ? kUsed : 0;         // overflow votes: their own words, or the idle first tile
-    static constexpr int kLdsBytes = kUsed + (kStream ? 64 : 0);
-    static constexpr bool kFits = D >= 32 && D % 8 == 0 && kLdsBytes <= kMaxLds &&
-                                  (!kBig || QB == 2);
-    // Waves per SIMD the register budget is sized for: two (256 registers
-    // each) when the LDS lets enough workgroups share a CU, else one, which
-    // leaves a wave up to 512 registers (the matrix-core registers then take
-    // what would otherwise spill to scratch) at no cost in occupancy.
-    static constexpr int kWgPerCu = kLdsBytes <= kMaxLds ? kMaxLds / kLdsBytes : 1;
-    static constexpr int kWavesPerSimd = kStream || kWgPerCu * kWaves >= 8 ? 2 : 1;
-};
 
 template <int ET, int D, bool STATS, bool OROWS, int GEO>
 __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerSimd)) void attn_fwd_lds_kernel(
@@ -985,27 +909,20 @@ hipError_t launch_kernel(const AttnArgs& a) {
     return hipGetLastError();
 }
 
-// The geometry with the largest workgroups whose grid still covers the 256 CUs
-// (the smallest one when none does).
 template <int ET, int D, bool STATS, bool OROWS>
 hipError_t launch_geo(const AttnArgs& a) {
-    const long long heads = (long long)a.B * a.H;
-    if (heads * ((a.Lq + 127) / 128) < 256) {
-        // keys split four ways (more waves per SIMD) once every split has at
-        // least two tiles; where the 128-row geometry streams only if one round of
-        // workgroups does it (B1 H8 L3960 D40, 496 workgroups: 41.0 us, against
-        // 31.8 in 248 of 128 rows)
-        const bool long_keys = a.Lk >= kQuarterMinKeys;
-        const bool one_round = heads * ((a.Lq + 63) / 64) <= 256;
-        if constexpr (Geom<D, kGeoQuarter>::kFits) {
-            if (long_keys && (one_round || !Geom<D, kGeoNormal>::kStream))
-                return launch_kernel<ET, D, STATS, OROWS, kGeoQuarter>(a);
-        }
-        if (!long_keys || one_round || !Geom<D, kGeoNormal>::kStream)
-            return launch_kernel<ET, D, STATS, OROWS, kGeoSmall>(a);
-    }
-    if constexpr (Geom<D, kGeoBig>::kFits) {
-        if (heads * ((a.Lq + 255) / 256) >= 256) return launch_kernel<ET, D, STATS, OROWS, kGeoBig>(a);
+    switch (pick_geometry<D>((long long)a.B * a.H, a.Lq, a.Lk)) {
+        case kGeoSmall: return launch_kernel<ET, D, STATS, OROWS, kGeoSmall>(a);
+        case kGeoQuarter:
+            if constexpr (Geom<D, kGeoQuarter>::kFits) return launch_kernel<ET, D, STATS, OROWS, kGeoQuarter>(a);
+            break;
+        case kGeoBig:
+            if constexpr (Geom<D, kGeoBig>::kFits) return launch_kernel<ET, D, STATS, OROWS, kGeoBig>(a);
+            break;
+        case kGeoPair:
+            if constexpr (Geom<D, kGeoPair>::kFits) return launch_kernel<ET, D, STATS, OROWS, kGeoPair>(a);
+            break;
+        default: break;
     }
     return launch_kernel<ET, D, STATS, OROWS, kGeoNormal>(a);
 }

@@ -107,3 +107,15 @@ def test_scales(D, scale):
 @pytest.mark.parametrize("D", [32, 40, 64, 80])
 def test_four_splits_with_an_empty_one(D, Lk, scale):
     check(1, 4, 150, Lk, D, 7900 + D + Lk, scale=None if scale is None else float(np.float32(scale)))
+
+
+# past one round of 128-row workgroups: two of them on a CU at D = 56 and 64 (two
+# buffers, no stream), with short, empty and ragged splits, and their fallback
+@pytest.mark.parametrize("Lk", [129, 192, 200, 320, 641])
+@pytest.mark.parametrize("D", [56, 64])
+def test_two_workgroups_a_cu(D, Lk):
+    check(1, 300, 128, Lk, D, 8900 + D + Lk)
+    if Lk in (200, 320):
+        check(3, 100, 70, Lk, D, 8950 + D + Lk, "bf16")
+        check(1, 260, 128, Lk, D, 8970 + D + Lk, q_mult=4.0)
+        check(1, 260, 128, Lk, D, 8990 + D + Lk, scale=0.0)
