@@ -202,10 +202,10 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
     }
 
     // With FOLD, acc sums a run of slices and tot the runs.  Past kSplitMinK
-    // channels that is the split-K kernel's order of summation, so a product has
-    // the same bits whichever kernel takes it; up to there the split kernel is
-    // not taken and one run saves the additions (1 us of 27 in the 64x64 level's
-    // convolution)
+    // channels that is the split-K kernel's order of summation, so a row has the
+    // same bits whichever kernel takes it, alone or in a batch of any size; up to
+    // there the split kernel is not taken and one run saves the additions (1 us of
+    // 27 in the 64x64 level's convolution)
     f32x16 acc[2], tot[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -577,16 +577,16 @@ hipError_t launch_group_e(LinGroup& g, const LinearArgs* a) {
     // 1280x640x640 (100) 7.7 -> 7.2, 36 products 32x1280x1280 31.3 -> 25.8.  From
     // there on the shared tiles are as fast or faster: 1024x1280x1280 (160 tiles)
     // 12.3 against 13.2, 3328x320x320 (130) 5.8 against 6.1, 36 products
-    // 72x1280x1280 34.4 against 41.9.  A single product splits only past
-    // kSplitMinK channels, so that its bits do not depend on its company in a
-    // launch; a batch (a convolution's products) has no other launch to match.
+    // 72x1280x1280 34.4 against 41.9.  Products split only past kSplitMinK
+    // channels, where the shared tiles sum in the same order (FOLD): a row's bits
+    // depend neither on its company in a launch nor on the other images of a batch.
     if (!xh) {
         long long tiles = 0;
         bool few_rows = true, may = true;
         for (int i = 0; i < g.n; ++i) {
             tiles += tiles_of(a[i], kBM, kBN) * a[i].batch;
             few_rows = few_rows && g.p[i].M <= 64;
-            may = may && (a[i].K > kSplitMinK || a[i].batch > 1);
+            may = may && a[i].K > kSplitMinK;
         }
         if (may && (tiles <= 128 || few_rows))
             return yh ? launch_ksplit<ET, true>(g, a) : launch_ksplit<ET, false>(g, a);
@@ -594,7 +594,7 @@ hipError_t launch_group_e(LinGroup& g, const LinearArgs* a) {
     const long long nblk = number_tiles(g, a, kBM, kBN);
     if (nblk > 0x7fffffff) return hipErrorInvalidValue;
     bool fold = false;
-    for (int i = 0; i < g.n; ++i) fold = fold || (a[i].K > kSplitMinK && a[i].batch == 1);
+    for (int i = 0; i < g.n; ++i) fold = fold || a[i].K > kSplitMinK;
     void* s = a[0].stream;
     if (xh) return yh ? launch_f<ET, true, true>(g, nblk, fold, s) : launch_f<ET, true, false>(g, nblk, fold, s);
     return yh ? launch_f<ET, false, true>(g, nblk, fold, s) : launch_f<ET, false, false>(g, nblk, fold, s);

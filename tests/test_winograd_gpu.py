@@ -158,3 +158,13 @@ def test_conv3x3_unet_levels_sampled_channels(level):
     x, w, b = make(2, C, C, L, L, 9200 + C + L)
     co = np.sort(np.random.default_rng(C + L).choice(C, size=8, replace=False))
     check(x, w, b, co=co)
+
+
+# an image alone (few rows: the products may split) and in a batch of 40 (160 rows)
+@pytest.mark.parametrize("Ci", [64, 320, 512, 520, 640])
+def test_conv3x3_bits_do_not_depend_on_the_batch(Ci):
+    x, w, b = make(40, Ci, 320, 8, 8, 9400 + Ci)
+    whole = run_conv(x, w, b)
+    for i in (0, 17, 39):
+        assert np.array_equal(run_conv(x[i:i + 1], w, b)[0], whole[i]), i
+    assert np.array_equal(run_conv(x[3:13], w, b), whole[3:13])
