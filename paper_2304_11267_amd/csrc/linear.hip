@@ -201,33 +201,13 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
             }
     }
 
-    // With FOLD, acc sums a run of slices and tot the runs.  Past kSplitMinK
-    // channels that is the split-K kernel's order of summation, so a row has the
-    // same bits whichever kernel takes it, alone or in a batch of any size; up to
-    // there the split kernel is not taken and one run saves the additions (1 us of
-    // 27 in the 64x64 level's convolution)
-    f32x16 acc[2], tot[2];
+    // acc += slice i (FIRST: acc = slice i); before() is issued while the slice's
+    // operands come from LDS
+    f32x16 zero;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = tot[t][r] = 0.0f;
-    const int run = FOLD && K > kSplitMinK ? (nk + kRuns - 1) / kRuns : nk;
-
-#pragma unroll
-    for (int i = 0; i < kStages - 1; ++i)
-        if (i < nk) issue(i);
-
-    for (int i = 0, left = run; i < nk; ++i, --left) {
-        if (FOLD && left == 0) {
-            left = run;
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    tot[t][r] += acc[t][r];
-                    acc[t][r] = 0.0f;
-                }
-        }
+    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+    auto slice = [&](int i, auto first_c, f32x16 (&acc)[2], auto before) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_c)::value;
         wait_slices(min(nk - 1 - i, kStages - 2));
         lds_barrier();   // slice i is in LDS for every wave; slot (i - 1) % kStages is free
         if (i + kStages - 1 < nk) issue(i + kStages - 1);
@@ -241,6 +221,7 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
             af[0][s] = *(const u32x4*)(st + offw[0][s]);
             af[1][s] = *(const u32x4*)(st + offw[1][s]);
         }
+        before();
         if (kval < kBK) {
 #pragma unroll
             for (int s = 0; s < 4; ++s)
@@ -252,9 +233,36 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            acc[0] = mfma32x32x16<ET>(af[0][s], bf[s], acc[0]);
-            acc[1] = mfma32x32x16<ET>(af[1][s], bf[s], acc[1]);
+            acc[0] = mfma32x32x16<ET>(af[0][s], bf[s], FIRST && s == 0 ? zero : acc[0]);
+            acc[1] = mfma32x32x16<ET>(af[1][s], bf[s], FIRST && s == 0 ? zero : acc[1]);
         }
+    };
+
+#pragma unroll
+    for (int i = 0; i < kStages - 1; ++i)
+        if (i < nk) issue(i);
+
+    // With FOLD, acc sums a run of slices and tot the runs before it.  Past
+    // kSplitMinK channels that is the split-K kernel's order of summation, so a
+    // row has the same bits whichever kernel takes it, alone or in a batch of any
+    // size; up to there the split kernel is not taken and one run does (the 64x64
+    // level's convolution 27 us against 28).  The additions cost a wave that has its
+    // SIMD to itself 5 clocks each, beside MFMAs too: without / with them 2048x640x640
+    // 7.2 / 7.5 us (7.9 with them in the loop of every slice), 1024x1280x1280 11.3 /
+    // 11.4 (12.0), 2048x2560x640 19.4 / 19.0 (20.0).
+    f32x16 acc[2] = {zero, zero}, tot[2] = {zero, zero};
+    const int run = FOLD && K > kSplitMinK ? (nk + kRuns - 1) / kRuns : nk;
+    for (int i0 = 0; i0 < nk; i0 += run) {
+        slice(i0, std::true_type{}, acc, [&]() __attribute__((always_inline)) {
+            if (FOLD && i0 > 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                tot[0] += acc[0];
+                tot[1] += acc[1];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+        for (int i = i0 + 1; i < min(i0 + run, nk); ++i) slice(i, std::false_type{}, acc, [] {});
+        if (!FOLD) break;
     }
 
     // Stage the 128 x 64 output tile (bias added, rounded) in LDS, rows of
