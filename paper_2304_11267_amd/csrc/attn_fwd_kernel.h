@@ -83,6 +83,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     uint16_t* __restrict__ O, float* __restrict__ LS, int Lq, int Lk, float scale_abs, float c,
     float bias, int neg, int nqb, int oh) {
     using G = Geom<D, GEO>;
+    static_assert(!G::kStream || G::QB == 2, "the streaming loop's step x works on query block x");
     constexpr int DK = G::DK;
     constexpr int DN = G::DN;
     constexpr int DD = G::DD;
@@ -404,7 +405,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
 #pragma unroll
             for (int s = 0; s < DK; ++s) {
                 u32x4 a = *(const u32x4*)(smem + buf + k_off + (32 * sub * D + 16 * s) * 2);
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < QB; ++j) st[sub][j] = mfma32x32x16<ET>(a, qreg[j][s], st[sub][j]);
             }
         };
@@ -590,15 +591,14 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
         constexpr int kIn = STATS ? 3 : 2, kOut = G::kOnes ? 1 : 2;
         constexpr int kOps = 8 * (kIn + 2 + kOut);
         auto softmax_op = [&](int x, int i) __attribute__((always_inline)) {
-            const int blk = QB == 2 ? x : 0;
             int at = 0;
 #pragma unroll
             for (int t = 0; t < 10; ++t) {
                 if (t < 8) {
                     if (STATS) {
-                        if (i == at) s_max[blk] = fmaxf(s_max[blk], fmaxf(st[x][2 * t], st[x][2 * t + 1]));
-                        if (i == at + 1) st[x][2 * t] = fmaf(st[x][2 * t], c, negm[blk]);
-                        if (i == at + 2) st[x][2 * t + 1] = fmaf(st[x][2 * t + 1], c, negm[blk]);
+                        if (i == at) s_max[x] = fmaxf(s_max[x], fmaxf(st[x][2 * t], st[x][2 * t + 1]));
+                        if (i == at + 1) st[x][2 * t] = fmaf(st[x][2 * t], c, negm[x]);
+                        if (i == at + 2) st[x][2 * t + 1] = fmaf(st[x][2 * t + 1], c, negm[x]);
                     } else {
                         if (i == at) st[x][2 * t] *= c;
                         if (i == at + 1) st[x][2 * t + 1] *= c;
@@ -613,7 +613,7 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
                 if (t >= 2) {
                     const int w = t - 2;
                     if (i == at) pk[x][w / 4][w % 4] = pack2<ET>(st[x][2 * w], st[x][2 * w + 1]);
-                    if (!G::kOnes && i == at + 1) l_part[blk] = add_pair<ET>(pk[x][w / 4][w % 4], l_part[blk]);
+                    if (!G::kOnes && i == at + 1) l_part[x] = add_pair<ET>(pk[x][w / 4][w % 4], l_part[x]);
                     at += kOut;
                 }
             }
@@ -625,15 +625,13 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             return m;
         };
         auto s_mfma = [&](int x, int sub, int s) __attribute__((always_inline)) {
-            const int blk = QB == 2 ? x : 0;
-            st[x] = mfma32x32x16<ET>(kf[sub][s], qreg[blk][s], s == 0 ? cin[blk] : st[x]);
+            st[x] = mfma32x32x16<ET>(kf[sub][s], qreg[x][s], s == 0 ? cin[x] : st[x]);
         };
         auto o_mfma = [&](int x, int sub, int h) __attribute__((always_inline)) {
-            const int blk = QB == 2 ? x : 0;
             if (G::kSparse && h == 2 * DD)
-                acc[blk][DN - 1] = smfmac32x32x32<ET>(vsf[sub], pk[x][0], pk[x][1], acc[blk][DN - 1], v_idx);
+                acc[x][DN - 1] = smfmac32x32x32<ET>(vsf[sub], pk[x][0], pk[x][1], acc[x][DN - 1], v_idx);
             else
-                acc[blk][h % DD] = mfma32x32x16<ET>(vf[sub][h / DD][h % DD], pk[x][h / DD], acc[blk][h % DD]);
+                acc[x][h % DD] = mfma32x32x16<ET>(vf[sub][h / DD][h % DD], pk[x][h / DD], acc[x][h % DD]);
         };
         // Step of parity X on sub-tile s (its place SUB in the tile).  Step 0 reads the
         // K of sub-tile s + 2 (kbuf), step 1 the V of s + 1 (vbuf): a whole sub-tile
@@ -685,12 +683,11 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             }
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
-                const int blk = QB == 2 ? x : 0;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     if (!STATS) {
-                        st[x][r] -= m_run[blk];
-                        cin[blk][r] = -m_run[blk];
+                        st[x][r] -= m_run[x];
+                        cin[x][r] = -m_run[x];
                     }
             }
             if (STATS) s_max[0] = max_of(0);
@@ -741,7 +738,9 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
             l_part[0] = l_last;
         }
         // a ragged last tile is the one after the whole ones; its copy has been
-        // waited for by the barrier of the step before
+        // waited for by the barrier of the step before.  (consume's way for a whole
+        // tile is never taken from here; without it the compiler spills 24 to 69 of
+        // the loop's registers: 300 keys D = 40 7.2 -> 8.3 us)
         if (n_whole < t_count) {
             const int t = t_first + n_whole, b = n_whole % SL;
             if (n_whole > 0) consume(fixed_c, fixed_c, t, b);

@@ -81,9 +81,10 @@ struct Geom {
     // Waves per SIMD the register budget is sized for: two (256 registers
     // each) when the LDS lets enough workgroups share a CU, else one, which
     // leaves a wave up to 512 registers (the matrix-core registers then take
-    // what would otherwise spill to scratch) at no cost in occupancy.
+    // what would otherwise spill to scratch) at no cost in occupancy.  (The
+    // streaming loop keeps 256 also for the odd waves of three workgroups a CU.)
     static constexpr int kWgPerCu = kLdsBytes <= kMaxLds ? kMaxLds / kLdsBytes : 1;
-    static constexpr int kWavesPerSimd = kStream || kWgPerCu * kWaves >= 8 ? 2 : 1;
+    static constexpr int kWavesPerSimd = kWgPerCu * kWaves >= (kStream ? 5 : 8) ? 2 : 1;
 };
 
 // The geometry of a call over `heads` (batch, head) pairs.  What counts is how

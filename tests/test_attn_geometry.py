@@ -104,3 +104,12 @@ def test_past_one_round_a_cu_has_eight_waves(picks):
         rows, waves, lds, _ = geom[D, g]
         if rounds(heads, Lq, rows) > 1 and rows > 64:
             assert LDS // lds * waves >= 8, (D, heads, Lq, Lk, g)
+
+
+def test_register_budget_follows_the_waves_on_a_cu(picks):
+    """512 registers where the LDS leaves each SIMD one wave, 256 from two on."""
+    geom, _ = picks
+    for key, (rows, waves, lds, per_simd) in geom.items():
+        on_cu = LDS // lds * waves
+        if on_cu <= 4 or on_cu >= 8:
+            assert per_simd == (1 if on_cu <= 4 else 2), key
