@@ -58,13 +58,16 @@ struct Geom {
     // ring of three buffers per key split (five where a workgroup fills a CU and
     // meets only every second tile); the other loop takes two.  It needs two
     // query blocks a wave (each LDS operand then feeds two MFMAs; with one the LDS
-    // is as busy as the matrix core).  16 heads, us: 4096 keys D = 40 62.1 -> 56.1,
-    // D = 64 86.5 -> 76.0, D = 32 55.1 -> 52.3, D = 48 64.5 -> 65.5; 2048 keys
-    // D = 64 28.3 -> 25.3, D = 48 21.6 -> 20.1; 300 keys D = 40 7.9 -> 6.8.  The four
-    // key splits of kGeoQuarter leave it too few tiles each (1024 keys D = 40 9.5
-    // -> 10.1).
+    // is as busy as the matrix core).  16 heads of as many rows as keys, the other
+    // loop / this one, us: 4096 keys D = 32 49.9 / 47.4, D = 40 56.6 / 52.6, D = 64
+    // 82.1 / 75.2; 2048 keys D = 64 26.8 / 23.3, D = 48 20.8 / 18.8; 2048 rows of 300
+    // keys D = 40 8.3 / 7.1.  Not for D = 48 in 256 rows, the one width that it
+    // measured slower at (why, is not known): 4096 keys 59.7 / 60.4, 2048 32.1 / 33.0,
+    // with statistics 65.2 / 66.2.  The four key splits of kGeoQuarter leave it too few
+    // tiles each (1024 keys D = 40 9.5 / 10.1).
     static constexpr int kRoom = kMaxLds - 64 - kConstBytes;
-    static constexpr bool kStream = QB == 2 && !kQuarter && GEO != kGeoPair && kKS * 3 * kBufBytes <= kRoom;
+    static constexpr bool kStream = QB == 2 && !kQuarter && GEO != kGeoPair && !(kBig && D == 48) &&
+                                    kKS * 3 * kBufBytes <= kRoom;
     static constexpr int kSlots = !kStream ? 2 : kBig && kKS * 5 * kBufBytes <= kRoom ? 5 : 3;
     static constexpr int kStep = kSlots == 5 ? 2 : 1;         // tiles between two barriers of the streaming loop
     static constexpr int kHalfBytes = kSlots * kBufBytes;

@@ -56,16 +56,17 @@ def check(B, H, Lq, Lk, D, seed, dtype="f16", scale=None, q_mult=1.0, grow=False
             assert np.all(np.abs(got[:, 1] / rs.reshape(-1) - 1) <= eps + tol)
 
 
-# 2 key splits of 64-key tiles in the 128-row and 256-row geometries (4 and 5
-# buffers' wrap-around), D = 40 and 56 streaming
+# 2 key splits of 64-key tiles in the 128-row geometry (a ring of three buffers)
 @pytest.mark.parametrize("Lk", [129, 192, 255, 256, 257, 449, 640, 705, 1031])
-@pytest.mark.parametrize("D", [40, 56])
+@pytest.mark.parametrize("D", [40, 56, 64])
 def test_stream_128_rows(D, Lk):
     check(2, 8, 2048, Lk, D, 900 + D + Lk)
 
 
-@pytest.mark.parametrize("Lk", [130, 321, 640, 1000])
-@pytest.mark.parametrize("D", [40, 64])
+# and in 256 rows (D = 64 at any key count, the others from 1024 on): five buffers
+# (D = 40), three (D = 64), or two and no stream (D = 48)
+@pytest.mark.parametrize("Lk", [130, 321, 640, 1000, 1024, 1030, 1100, 1313])
+@pytest.mark.parametrize("D", [40, 48, 64])
 def test_stream_256_rows(D, Lk):
     check(2, 8, 4096, Lk, D, 1900 + D + Lk)
 
