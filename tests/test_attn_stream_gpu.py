@@ -120,3 +120,54 @@ def test_two_workgroups_a_cu(D, Lk):
         check(3, 100, 70, Lk, D, 8950 + D + Lk, "bf16")
         check(1, 260, 128, Lk, D, 8970 + D + Lk, q_mult=4.0)
         check(1, 260, 128, Lk, D, 8990 + D + Lk, scale=0.0)
+
+
+# NaN and infinite inputs: wherever the definition gives NaN or Inf so does every
+# path (streaming in each geometry, four splits, two buffers, a maximum that
+# moves), and other heads keep their bits.  The kernels' maxima are compiled for
+# finite scores: this is what shows that nothing else takes a NaN for a number.
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 4, 150, 300, 40), (1, 4, 150, 600, 40), (1, 4, 150, 600, 64),
+                                   (2, 8, 2048, 330, 40), (2, 8, 4096, 1030, 40), (1, 16, 2048, 300, 64),
+                                   (1, 300, 128, 200, 64), (1, 4, 150, 320, 80), (1, 4, 150, 1000, 160),
+                                   (2, 8, 2048, 300, 160)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_nan_and_infinity_stay(shape, dtype):
+    import torch
+    B, H, Lq, Lk, D = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Lk + D)
+    dt = torch.float16 if dtype == "f16" else torch.bfloat16
+    clean = [torch.randn(B, H, n, D, device="cuda", generator=g).to(dt) for n in (Lq, Lk, Lk)]
+    scale = float(np.float32(1 / np.sqrt(D)))
+
+    def run(q, k, v, stats):
+        out = torch.full_like(q, 7.0)
+        ls = torch.full((B, H, Lq, 2), 7.0, dtype=torch.float32, device="cuda") if stats else None
+        sd.forward_ex(q, k, v, out, scale, ls=ls)
+        torch.cuda.synchronize()
+        return out, ls
+
+    nan, inf = float("nan"), float("inf")
+    # which of q, k, v; row; column; value
+    for where, row, col, bad in ((0, Lq - 1, 3, nan), (0, 5, D - 1, inf), (1, 0, 0, nan), (1, Lk - 1, D - 1, nan),
+                                 (1, Lk // 2, 1, -inf), (2, Lk - 1, 0, nan), (2, 1, D - 1, inf)):
+        ins = [t.clone() for t in clean]
+        ins[where][0, 1, row, col] = bad
+        q, k, v = (t[0, 1].double() for t in ins)
+        a = (q @ k.t().contiguous()) * scale
+        p = torch.softmax(a, dim=1)
+        ref = p @ v
+        for stats in (False, True):
+            out, ls = run(*ins, stats)
+            got = out[0, 1].double()
+            assert not torch.isfinite(got[~torch.isfinite(ref)]).any(), (where, row, bad, stats)
+            if stats:
+                lost = ~torch.isfinite(p).all(dim=1)
+                assert not torch.isfinite(ls[0, 1][lost][:, 1]).any(), (where, row, bad)
+            same, same_ls = run(*clean, stats)
+            keep = torch.ones(B, H, dtype=torch.bool, device="cuda")
+            keep[0, 1] = False
+            assert torch.equal(out[keep], same[keep])
+            if stats:
+                assert torch.equal(ls[keep], same_ls[keep])
