@@ -22,9 +22,12 @@ def _needs_gpu():
 
 
 SHAPES = [
-    # (L, K, N): 32x32 tiles, then 32x64, then past the rule
-    (1, 8, 8), (31, 56, 24), (33, 520, 40), (32, 584, 32), (65, 648, 72), (100, 1096, 136),
-    (32, 1280, 1288), (257, 528, 640), (512, 1280, 1280), (1000, 776, 520), (1664, 648, 640),
+    # (L, K, N): too few channels for the rule; 32x32 tiles; 32x64; 64x64; past the rule
+    (1, 8, 8), (31, 56, 24),
+    (33, 520, 40), (32, 584, 32), (65, 648, 72), (100, 1096, 136), (32, 1280, 1288),
+    (257, 528, 640), (512, 1280, 1280), (1000, 776, 520),
+    (64, 520, 32768), (50, 584, 32712),
+    (1664, 648, 640),
 ]
 
 
@@ -49,7 +52,9 @@ def test_split_product_matches_oracle(shape, heads):
     assert np.all(np.abs(g - r) <= bound), float(np.max(np.abs(g - r) / bound))
 
 
-@pytest.mark.parametrize("K", [40, 320, 520, 768])
+# 520: runs of 3, 3, 3 and no slices; 584: 3, 3, 3 and 1 of 8 channels; up to 512
+# channels no call splits
+@pytest.mark.parametrize("K", [40, 320, 520, 584, 768, 1280])
 def test_split_product_has_the_shared_tiles_bits(K):
     import torch
     g = torch.Generator(device="cuda")
@@ -58,7 +63,7 @@ def test_split_product_has_the_shared_tiles_bits(K):
     w = (torch.randn(320, K, device="cuda", generator=g) / K ** 0.5).half()
     tall = torch.empty(1, 8192, 320, dtype=torch.float16, device="cuda")
     sd.linear(x, w, tall)                       # 320 shared tiles
-    for rows in (1, 154, 1024):                 # 32x32 and 32x64 split tiles
+    for rows in (1, 154, 1024):                 # 32x32 and (1024 rows) 32x64 split tiles
         part = torch.empty(1, rows, 320, dtype=torch.float16, device="cuda")
         sd.linear(x[:, :rows].contiguous(), w, part)
         assert torch.equal(part, tall[:, :rows]), rows

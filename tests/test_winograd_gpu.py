@@ -160,6 +160,18 @@ def test_conv3x3_unet_levels_sampled_channels(level):
     check(x, w, b, co=co)
 
 
+# products of 33 to 64 rows over two CUs' worth of 64x64 tiles: whole and ragged
+# rows, ragged channels, an empty last run of input channels (520: slices 3 + 3 + 3 + 0)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 1280, 1280, 20, 20), (1, 520, 920, 32, 32), (2, 584, 1000, 20, 18)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_conv3x3_split_64x64_tiles(shape, dtype):
+    B, Ci, Co, H, W = shape
+    x, w, b = make(B, Ci, Co, H, W, 9300 + Ci + W, dtype)
+    co = np.sort(np.random.default_rng(Ci).choice(Co, size=8, replace=False))
+    check(x, w, b, dtype=dtype, co=np.union1d(co, [0, Co - 1]))
+
+
 # an image alone (few rows: the products may split) and in a batch of 40 (160 rows)
 @pytest.mark.parametrize("Ci", [64, 320, 512, 520, 640])
 def test_conv3x3_bits_do_not_depend_on_the_batch(Ci):
