@@ -50,7 +50,14 @@ def test_same_bits_and_errors_as_ctypes(native, monkeypatch):
     side = torch.cuda.Stream()
 
     def calls(stream):
-        o = torch.empty_like(q)
+        on = stream or torch.cuda.current_stream()
+        on.wait_stream(torch.cuda.current_stream())
+
+        def now(t):   # t's values after the calls so far
+            on.synchronize()
+            return t.clone()
+
+        o = torch.full_like(q, 7.0)
         ls = torch.empty(2, 8, 70, 2, device="cuda")
         a = torch.empty(2, 8, 70, 90, dtype=torch.float32, device="cuda")
         p = torch.empty(2 * 8 * 70, 90, device="cuda")
@@ -59,10 +66,13 @@ def test_same_bits_and_errors_as_ctypes(native, monkeypatch):
         c = torch.empty(2, 16, 9, 12, dtype=torch.float16, device="cuda")
         n, n2 = torch.empty_like(img), torch.empty_like(img)
         e = torch.empty(2, 70, 160, dtype=torch.float16, device="cuda")
-        out = [sd.forward(q, k, v, o, 0.2, stream).clone()]
-        out += [sd.forward_ex(q, k, v, o, 0.2, ls=ls, stream=stream).clone(), ls.clone()]
+        torch.cuda.synchronize()
+        out = [now(sd.forward(q, k, v, o, 0.2, stream))]
+        o.fill_(7.0)
+        torch.cuda.synchronize()
+        out += [now(sd.forward_ex(q, k, v, o, 0.2, ls=ls, stream=stream)), now(ls)]
         out += [sd.logits(q, k, a, 0.2, stream)]
-        out += [sd.softmax_rows(a.view(-1, 90), ls.view(-1, 2), p, 1.0, stream).clone(), p]
+        out += [now(sd.softmax_rows(a.view(-1, 90), ls.view(-1, 2), p, 1.0, stream)), p]
         out += [sd.softmax_pv(a, ls, v, torch.empty_like(q), stream)]
         out += [sd.attention_block(x, ctx, wq, wk, wv, wo, bo, y, ws, 8, 0.1, stream)]
         out += [sd.attention_block_kv(x, wq, kh, vh, wo, None, y2, ws, 0.1, stream)]
@@ -71,8 +81,34 @@ def test_same_bits_and_errors_as_ctypes(native, monkeypatch):
         torch.cuda.synchronize()
         return out
 
+    def reads_in_order(call, src):
+        """Whether call(stream), on a side stream, sees the values that a copy queued there
+        before it gives src."""
+        old, new = src.clone(), src.flip(0).contiguous()
+        want = call(None, new).clone()
+        for stream, current in ((side, torch.cuda.current_stream()), (None, side)):
+            src.copy_(old)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                torch.cuda._sleep(10_000_000)   # some milliseconds
+                src.copy_(new)
+            with torch.cuda.stream(current):
+                got = call(stream, src)
+            torch.cuda.synchronize()
+            if not torch.equal(got, want):
+                return False
+        src.copy_(old)
+        torch.cuda.synchronize()
+        return True
+
     rnd_c = rnd(24)
     torch.cuda.synchronize()
+    outs = [torch.empty_like(t) for t in (q, x, img)]
+    big = torch.empty(1 << 22, dtype=torch.uint8, device="cuda")
+    assert reads_in_order(lambda s, t: sd.forward(t, k, v, outs[0], 0.2, s), q)
+    assert reads_in_order(lambda s, t: sd.forward_ex(t, k, v, outs[0], 0.2, stream=s), q)
+    assert reads_in_order(lambda s, t: sd.attention_block(t, ctx, wq, wk, wv, wo, bo, outs[1], big, 8, 0.1, s), x)
+    assert reads_in_order(lambda s, t: sd.group_norm(t, 8, outs[2], stream=s), img)
     fast = [calls(None), calls(side)]
     with torch.cuda.stream(side):
         fast.append(calls(None))
