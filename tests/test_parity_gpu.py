@@ -94,7 +94,7 @@ def test_unet_case_bf16(name):
 @pytest.mark.parametrize("name,per_head", [("l32_self", 48), ("l64_self", 24)])
 def test_unet_case_bf16_sampled_rows(name, per_head):
     """The 32x32 self-attention (64-row workgroups, keys split four ways) and
-    the 64x64 one (256-row workgroups, 128-key tiles) in bf16."""
+    the 64x64 one (256-row workgroups) in bf16."""
     case = wl.CASES[name]
     q, k, v = wl.case_inputs(case, dtype="bf16")
     rows = wl.sample_rows(case.B, case.H, case.Lq, per_head, seed=case.seed + 7)
@@ -158,9 +158,9 @@ def test_statistics_output_does_not_change_o(Lk, D):
     assert np.array_equal(o_plain, o_stats)
 
 
-# Grids of at least 256 workgroups of 256 query rows take the largest
-# geometry (eight waves, 128-key tiles) for D <= 64: a partial last query
-# block, a ragged last key tile in either half, every head width it covers.
+# Grids that 256 query rows a workgroup (eight waves) cover in one round and 128
+# in two, D <= 64: the former from 1024 keys on, or at any count for D = 64, else
+# the latter; a partial last query block, a ragged last key tile in either half.
 @pytest.mark.parametrize("Lk,D,dtype", [(1000, 40, "f16"), (1100, 32, "f16"), (900, 48, "f16"),
                                         (1000, 64, "f16"), (4095, 40, "f16"), (1000, 40, "bf16")])
 def test_large_grid_ragged(Lk, D, dtype):
@@ -458,13 +458,13 @@ def test_key_norms_growing_along_the_sequence(Lk, D):
 
 # ------------------- the workgroup geometries the UNet levels launch, with the
 # fixed-maximum fast path and its exact fallback.  B = 2, H = 8 at Lq = 4096
-# (D <= 64) fills the chip with 256-row workgroups of eight waves and 128-key
-# tiles (the 64x64 level); Lq = 2048 takes 128-row workgroups; the launch with
-# statistics always takes 128-row workgroups.  The overflow vote and the
-# online rerun run per workgroup, so only the heads whose keys are planted
-# take the fallback while the others stay on the fast path.
+# (D <= 64) fills the chip with 256-row workgroups of eight waves from 1024 keys
+# on (the 64x64 level); Lq = 2048 takes 128-row workgroups; with statistics
+# likewise.  The overflow vote and the online rerun run per workgroup, so only
+# the heads whose keys are planted take the fallback while the others stay on
+# the fast path.
 
-def _late_dominant_inputs(B, H, Lq, Lk, D, tile_keys, seed, dtype):
+def _late_dominant_inputs(B, H, Lq, Lk, D, seed, dtype):
     """q.k = 64 for a few keys past the first 32-key sub-tile of each key half
     (about 0 elsewhere) in the even heads: with scale 1 the rounded p of those
     keys overflows under a maximum fixed at the first sub-tile."""
@@ -474,9 +474,9 @@ def _late_dominant_inputs(B, H, Lq, Lk, D, tile_keys, seed, dtype):
     q[..., 1:] = rng.standard_normal((B, H, Lq, D - 1), dtype=np.float32) * 0.1
     k = rng.standard_normal((B, H, Lk, D), dtype=np.float32) * 0.1
     v = rng.standard_normal((B, H, Lk, D), dtype=np.float32)
-    ntiles = (Lk + tile_keys - 1) // tile_keys
+    ntiles = (Lk + 63) // 64
     nh = (ntiles + 1) // 2
-    for j in (40, 77, nh * tile_keys + 40, Lk - 1):
+    for j in (40, 77, nh * 64 + 40, Lk - 1):
         if j < Lk:
             k[:, ::2, j, 0] = 8.0
     if dtype == "bf16":
@@ -489,19 +489,15 @@ def _rows_with_edges(B, H, Lq, per_head, seed):
     return np.unique(np.concatenate([rows, [Lq - 1, Lq, 2 * Lq - 1, B * H * Lq - 1]]))
 
 
-@pytest.mark.parametrize("Lk,dtype", [(4096, "f16"), (4096, "bf16"), (700, "f16"), (350, "f16")])
+@pytest.mark.parametrize("Lk,dtype", [(4096, "f16"), (4096, "bf16"), (1030, "f16"), (700, "f16"), (350, "f16")])
 def test_big_geometry_late_dominant_keys_fall_back(Lk, dtype):
-    """256-row workgroups (plain launch) and 128-row ones (with statistics):
-    the eight-wave vote and the online rerun over 128-key tiles, including a
-    ragged last tile of key half 1 left pending in buffer 0 (Lk = 700 for
-    128-key tiles, Lk = 350 for 64-key tiles)."""
+    """256-row workgroups (from 1024 keys) and 128-row ones: the vote of eight or
+    four waves and the online rerun, including a ragged last tile of key half 1
+    left pending in buffer 0 (Lk = 350 and 700) or 1 (1030)."""
     B, H, Lq, D = 2, 8, 4096, 40
-    q, k, v = _late_dominant_inputs(B, H, Lq, Lk, D, 128, 5100 + Lk, dtype)
+    q, k, v = _late_dominant_inputs(B, H, Lq, Lk, D, 5100 + Lk, dtype)
     rows = _rows_with_edges(B, H, Lq, 24, seed=Lk)
     check_case(q, k, v, 1.0, dtype=dtype, rows=rows, what=f"big late-dominant Lk={Lk} {dtype}")
-    if Lk == 350:   # the 64-key tiles of the statistics launch: plant per its tiling too
-        q, k, v = _late_dominant_inputs(B, H, Lq, Lk, D, 64, 5200 + Lk, dtype)
-        check_case(q, k, v, 1.0, dtype=dtype, rows=rows, what=f"late-dominant 64-key tiles Lk={Lk}")
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -533,7 +529,7 @@ def test_128_row_geometry_plain_launch(D, variant):
         q, k, v = wl.make_qkv(B, H, Lq, Lk, D, 5400 + D)
         scale = float(np.float32(1 / np.sqrt(D)))
     else:
-        q, k, v = _late_dominant_inputs(B, H, Lq, Lk, D, 64, 5500 + D, "f16")
+        q, k, v = _late_dominant_inputs(B, H, Lq, Lk, D, 5500 + D, "f16")
         scale = 1.0
     rows = _rows_with_edges(B, H, Lq, 24, seed=D)
     check_case(q, k, v, scale, rows=rows, what=f"128-row Lq=2048 D={D} {variant}")
@@ -547,8 +543,8 @@ def test_bitwise_deterministic_at_the_64x64_level():
 
 
 # ------------- 64-row workgroups with the keys split four ways (eight waves):
-# the plain launch's geometry for grids of fewer than 256 128-row blocks once
-# Lk >= 512 and D <= 80 (the 32x32 level).  Split s takes tiles s*nh ..
+# taken from 512 keys on at D <= 80 where 64 rows need no more rounds over the
+# CUs than 128 (the 32x32 level).  Split s takes tiles s*nh ..
 # s*nh + nh - 1 (nh = ceil(ntiles / 4)); the last splits may be short or
 # empty.  These tiles carry no constant block, so the row sum comes from
 # v_dot2 and the padded d rows read V columns that are never stored.
