@@ -544,10 +544,9 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     // 277 interleaved, 314 as two runs.  m enters as the initial value of S^T,
     // so that one multiply is left before the exponential.  Pair p's S^T and
     // rounded p live in the buffers of p's parity.  64x64 level (B2 H8 L4096 D40):
-    // 62.0 -> 56.9 us; what bounds it is the power limit (the clock sits at 1.5 to
-    // 1.6 GHz) on 6 MFMAs, 16 exponentials and 24 other operations per pair, then
-    // the barriers, copies and LDS reads (35, 27 and 30 of 385 clocks a pair with
-    // a barrier per tile; one per two tiles and scalar copy addresses: 363).
+    // 56.6 -> 52.6 us; of a workgroup's 96.9 thousand clocks 88.4 are the loop's, 345 a
+    // pair and SIMD for 6 MFMAs, 16 exponentials and 24 other operations (277 bare)
+    // and the barriers, copies and LDS reads between them, at 1.9 to 2.0 GHz.
     auto stream_tiles = [&]() __attribute__((always_inline)) {
         constexpr int SL = G::kSlots;
         constexpr int NQ = DK;                                 // MFMAs of S^T
@@ -749,12 +748,13 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     };
 
     // With few tiles and one query block a moving m costs little beside the fixed
-    // part, and rows with large logits need no second pass: 16x16 level 8.2 us
-    // either way, with queries four times as long 12.6 -> 8.4; 32x32 level 12.3 ->
-    // 12.4 and 21.4 -> 12.6 (two query blocks: D = 64 there 12.2 -> 13.8, so not for
-    // them).  At large D a ragged tile's steps are code of their own to fetch
-    // (Lk 300, D = 160: 10.7 -> 11.9), so whole tiles only.  bf16 weights do not
-    // overflow.
+    // part, and rows with large logits need no second pass.  Fixed / moving, us, and with
+    // queries four times as long: 16 heads of 256 rows and keys D = 160 8.0 / 7.9, 11.8 /
+    // 8.0; 1024 rows, 512 keys D = 80 7.9 / 8.0, 11.6 / 8.0; 2048 rows, 512 keys D = 128
+    // 27.0 / 26.9, 46.2 / 26.9; 300 rows and keys (a ragged tile) D = 80 6.6 / 7.1, 11.0 /
+    // 7.4, the most that it costs (two query blocks: D = 64, 1024 keys 12.2 / 13.8, so not
+    // for them).  At large D a ragged tile's steps are code of their own to fetch (Lk
+    // 300, D = 160: 10.7 -> 11.9), so whole tiles only.  bf16 weights do not overflow.
     const bool direct = !G::kStream && QB == 1 && ET == kF16 && nh <= kDirectTiles &&
                         (DN <= 3 || Lk % kTK == 0);
     // Overflow vote: with m fixed at the first sub-tile's maximum - bias, a
