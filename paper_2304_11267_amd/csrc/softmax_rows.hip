@@ -89,21 +89,11 @@ __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s
     m = M;
 }
 
-// The group of rows of workgroup i: each XCD takes a contiguous run of them,
-// last rows first.  The logits kernel writes A and softmax_pv reads it with
-// every XCD going forwards through its run, so this pass meets what was written
-// last while it is still in the 256 MB cache behind the L2s, and leaves there
-// what softmax_pv reads first (the three calls with A of 537 MB: 355.4 -> 350.8 us).
-__device__ __forceinline__ long long row_group(long long i, long long ngroups) {
-    return ngroups == gridDim.x ? ngroups - 1 - xcd_remap((int)i, (int)ngroups) : i;
-}
-
-
 // WPR = waves per row (1 or 4); VEC = rows are read in 16-byte chunks.
 template <int ET, int WPR, bool VEC>
 __global__ __launch_bounds__(kThreads) void softmax_rows_kernel(
     const void* __restrict__ A, float* __restrict__ LS, void* __restrict__ P, long long rows,
-    long long cols, float scale, long long ngroups) {
+    long long cols, float scale, long long ngroups, int last_first) {
     constexpr int RPW = 4 / WPR;                 // rows per workgroup
     constexpr int EPC = VEC ? Elem<ET>::kPerChunk : 1;
     __shared__ float red[4][2];
@@ -115,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void softmax_rows_kernel(
     const long long stride = 64LL * WPR;
 
     for (long long i = blockIdx.x; i < ngroups; i += gridDim.x) {
-        const long long g = row_group(i, ngroups);
+        const long long g = last_first ? ngroups - 1 - i : i;
         const long long row = g * RPW + wave / WPR;
         const bool live = row < rows;
         float m = -__builtin_inff(), s = 0.0f;
@@ -194,8 +184,7 @@ __global__ __launch_bounds__(kThreads) void softmax_rows_reg_kernel(
     const int wave = threadIdx.x >> 6;
     const int nunits = (int)(cols / EPC);
 
-    for (long long it = blockIdx.x; it < ngroups; it += gridDim.x) {
-        const long long g = row_group(it, ngroups);
+    for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
         const long long row = g * 4 + wave;
         if (row >= rows) continue;   // no barriers below: waves are independent
         const long long base = row * nunits;
@@ -262,8 +251,17 @@ hipError_t launch3(const SoftmaxArgs& a) {
     constexpr int RPW = 4 / WPR;
     const long long ngroups = (a.rows + RPW - 1) / RPW;
     const long long grid = ngroups < kMaxGrid ? ngroups : kMaxGrid;
+    // An A that the 256 MB cache behind the L2s does not hold is visited last rows
+    // first: after the logits kernel this pass then meets what was written last while
+    // it is still there (the three calls with A of 537 MB 358 -> 350 us; the pass by
+    // itself 88.9 / 88.7, where a run of rows for each XCD took it to 99.8).  Up to
+    // there the order does not matter (268 MB 40.2 / 40.1); rows read value by value
+    // are slower that way (the three calls at 3001 tokens 940 / 968), and rows held in
+    // registers (134 MB 21.6 / 22.2).
+    const long long bytes = a.rows * a.cols * (16 / Elem<ET>::kPerChunk);
     hipLaunchKernelGGL((softmax_rows_kernel<ET, WPR, VEC>), dim3((unsigned)grid), dim3(kThreads), 0,
-                       (hipStream_t)a.stream, a.a, a.ls, a.p, a.rows, a.cols, a.scale, ngroups);
+                       (hipStream_t)a.stream, a.a, a.ls, a.p, a.rows, a.cols, a.scale, ngroups,
+                       VEC && bytes > (256LL << 20) ? 1 : 0);
     return hipGetLastError();
 }
 

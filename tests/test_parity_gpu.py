@@ -402,6 +402,23 @@ def test_softmax_rows_matches_oracle(rows, cols, dtype):
     assert psum <= {"f32": 1e-5, "f16": 2e-3, "bf16": 1.6e-2}[dtype], f"rows of p sum to 1 +- {psum:.3e}"
 
 
+@pytest.mark.parametrize("rows,cols", [(40001, 4000), (8195, 16392), (32768, 4096), (32769, 4096)])
+def test_softmax_rows_past_the_cache(rows, cols):
+    """More than 256 MB of rows are visited last first: the pairs of a call over
+    them are those of calls over a part, bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    a = torch.randn(rows, cols, device="cuda", generator=g).half()
+    ls = torch.full((rows, 2), 7.0, device="cuda")
+    sd.softmax_rows(a, ls)
+    for i in range(0, rows, 6007):
+        part = a[i:i + 6007]
+        pls = torch.full((part.shape[0], 2), 9.0, device="cuda")
+        sd.softmax_rows(part, pls)
+        assert torch.equal(pls, ls[i:i + 6007]), i
+
+
 def test_softmax_rows_without_p_and_negative_scale():
     a = wl.make_matrix(40, 4096, seed=11, dtype="f16")
     ls, _ = run_softmax_rows(a, -1.5, "f16", want_p=False)
