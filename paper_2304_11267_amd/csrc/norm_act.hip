@@ -14,7 +14,8 @@
 // statistics from the whole run (the later reads hit that XCD's L2) and writes
 // 1/S of the output, so the launch covers the chip.  Runs that do not start on
 // 16 bytes (HW not a multiple of 8) are read in the same aligned chunks, their
-// neighbours' values masked in the first and last.  Bound by the latency of one
+// neighbours' values masked in the first and last, but for the shortest
+// (launch_gn_e), which go value by value.  Bound by the latency of one
 // read, two reductions and one write: [2, 320, 64, 64] 5.7 us.  Against reading
 // value by value in one workgroup a group: [2, 320, 33, 62] 27.6 -> 6.1 us,
 // [2, 320, 90, 90] (runs past the registers) 99 -> 20.
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(kGnThreads) void gn_kernel(
     });
 }
 
-// Any group size: the three steps each read the run from memory.  (X and Y
+// Any group size, and short runs: the three steps each read the run from memory.  (X and Y
 // may be the same tensor in both kernels: a group is read completely before
 // its first value is written, and no other workgroup touches it.)
 template <int ET>
@@ -281,12 +282,18 @@ template <int ET>
 hipError_t launch_gn_e(const GroupNormArgs& a) {
     const long long n = (long long)(a.C / a.G) * a.HW;
     const unsigned grid = (unsigned)(a.B * a.G);
-    if (n < (1 << 30) && a.C / a.G <= kGnMaxCpg) {
+    const int ng = a.B * a.G;
+    const bool whole = a.HW % 8 == 0;
+    // Short runs that do not start on 16 bytes go value by value: the chunks' masks
+    // and registers cost more than they save (value by value / in chunks, us: 64
+    // groups of 1400 values 4.3 / 4.6, of 2000 4.9 / 4.9, of 3000 5.9 / 5.0; of 160 3.0 /
+    // 4.5), all the more where the registers leave a CU one workgroup (512 groups of
+    // 4000 8.5 / 9.1, of 6000 11.3 / 9.9; 1024 of 5000 13.3 / 17.7, of 8000 23.5 / 20.1).
+    const bool short_run = !whole && n < (ng <= 256 ? 2000 : ng <= 512 ? 5000 : 6500);
+    if (n < (1 << 30) && a.C / a.G <= kGnMaxCpg && !short_run) {
         // several workgroups per group when there are few groups, unless in place
-        const int ng = a.B * a.G;
         const int S = (ng >= 256 || a.x == a.y) ? 1 : ng >= 128 ? 2 : 4;
         const unsigned grid8 = (unsigned)((ng + 7) / 8 * 8 * S);
-        const bool whole = a.HW % 8 == 0;
         const bool resident = n + (whole ? 0 : 14) <= kGnResident;
         auto pick = [&](auto s_c) {
             constexpr int K = decltype(s_c)::value;

@@ -23,11 +23,19 @@ def _needs_gpu():
 
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("shape", [
-    (1, 5, 3, 5),            # groups of three values
+    (1, 5, 3, 5),            # value by value: groups of three values
     (3, 21, 7, 7),           # channels shorter than a chunk, three to a group
+    (4, 160, 63, 32),
+    (9, 64, 65, 32),
+    (2, 1332, 3, 2),         # 1998 values: the last so
+    (2, 1336, 3, 2),         # 2004: in chunks, channels shorter than one
+    (3, 640, 7, 2),
     (2, 320, 33 * 62, 32),   # four workgroups a group
-    (4, 160, 63, 32),        # two
-    (9, 64, 65, 32),         # one
+    (4, 640, 125, 32),       # two
+    (9, 640, 249, 32),       # 288 groups of 4980: value by value
+    (9, 640, 251, 32),       # of 5020: in chunks, one workgroup a group
+    (17, 640, 323, 32),      # 544 groups of 6460 and 6500
+    (17, 640, 325, 32),
     (1, 96, 16381, 32),      # 49143 values: past the registers only by alignment
     (1, 96, 16384, 32),      # 49152: the last that fits
     (2, 96, 18001, 32),      # 54003: three reads, misaligned
