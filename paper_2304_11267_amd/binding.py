@@ -7,10 +7,12 @@ arithmetic of the attention happens here.  The library is loaded from the
 package directory on first use; a missing library raises, there is no other
 code path.
 
-The calls of a denoising loop are marshalled by the extension module _marshal
-(csrc/marshal.cpp): 10 us of Python and ctypes a call, as long as two of the
-smaller kernels, against 3.  What it does not take (it answers None) goes
-through ctypes below, which also raises the errors.
+Ten functions are marshalled by the extension module _marshal (csrc/marshal.cpp):
+forward, forward_ex, softmax_rows, logits, softmax_pv, attention_block,
+attention_block_kv, group_norm, geglu and conv3x3, in 3 us a call where Python
+and ctypes take 10, as long as two of the smaller kernels.  linear,
+attention_block_static, project_kv and winograd_weights go through ctypes below,
+as does what the module does not take (it answers None); errors are raised there.
 """
 from __future__ import annotations
 

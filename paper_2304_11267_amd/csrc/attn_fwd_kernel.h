@@ -546,7 +546,8 @@ __global__ __launch_bounds__((Geom<D, GEO>::kThreads), (Geom<D, GEO>::kWavesPerS
     // rounded p live in the buffers of p's parity.  64x64 level (B2 H8 L4096 D40):
     // 56.6 -> 52.6 us; of a workgroup's 96.9 thousand clocks 88.4 are the loop's, 345 a
     // pair and SIMD for 6 MFMAs, 16 exponentials and 24 other operations (277 bare)
-    // and the barriers, copies and LDS reads between them, at 1.9 to 2.0 GHz.
+    // and the barriers, copies and LDS reads between them, at 1.9 to 2.0 GHz; in runs of
+    // seconds the power limit takes the clock to about 1.65 GHz, and a launch 61 us.
     auto stream_tiles = [&]() __attribute__((always_inline)) {
         constexpr int SL = G::kSlots;
         constexpr int NQ = DK;                                 // MFMAs of S^T
