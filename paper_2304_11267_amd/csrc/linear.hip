@@ -251,10 +251,43 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
     // 7.2 / 7.5 us (7.9 with them in the loop of every slice), 1024x1280x1280 11.3 /
     // 11.4 (12.0), 2048x2560x640 19.4 / 19.0 (20.0).
     f32x16 acc[2] = {zero, zero}, tot[2] = {zero, zero};
-    const int run = FOLD && K > kSplitMinK ? (nk + kRuns - 1) / kRuns : nk;
+    const int run = K > kSplitMinK ? (nk + kRuns - 1) / kRuns : nk;
+    if constexpr (!FOLD) {
+        // (a loop of its own: as slices opened by a run's first one, products with a
+        // ragged last slice were slower, 8192x328x320 8.7 -> 9.1 us)
+        for (int i = 0; i < nk; ++i) {
+            wait_slices(min(nk - 1 - i, kStages - 2));
+            lds_barrier();   // slice i is in LDS for every wave; slot (i - 1) % kStages is free
+            if (i + kStages - 1 < nk) issue(i + kStages - 1);
+            const char* st = smem + (i % kStages) * kSliceBytes;
+            const int kval = K - i * kBK;    // channels of this slice inside K (uniform)
+            // all twelve operand reads first, so their latencies overlap
+            u32x4 bf[4], af[2][4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                bf[s] = *(const u32x4*)(st + offx[s]);
+                af[0][s] = *(const u32x4*)(st + offw[0][s]);
+                af[1][s] = *(const u32x4*)(st + offw[1][s]);
+            }
+            if (kval < kBK) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (8 * (2 * s + half) >= kval) {
+                        bf[s] = u32x4{0u, 0u, 0u, 0u};
+                        af[0][s] = bf[s];
+                        af[1][s] = bf[s];
+                    }
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                acc[0] = mfma32x32x16<ET>(af[0][s], bf[s], acc[0]);
+                acc[1] = mfma32x32x16<ET>(af[1][s], bf[s], acc[1]);
+            }
+        }
+    } else
     for (int i0 = 0; i0 < nk; i0 += run) {
         slice(i0, std::true_type{}, acc, [&]() __attribute__((always_inline)) {
-            if (FOLD && i0 > 0) {
+            if (i0 > 0) {
                 __builtin_amdgcn_sched_barrier(0);
                 tot[0] += acc[0];
                 tot[1] += acc[1];
@@ -262,7 +295,6 @@ __global__ __launch_bounds__(256) void linear_kernel(const LinGroup grp) {
             }
         });
         for (int i = i0 + 1; i < min(i0 + run, nk); ++i) slice(i, std::false_type{}, acc, [] {});
-        if (!FOLD) break;
     }
 
     // Stage the 128 x 64 output tile (bias added, rounded) in LDS, rows of
